@@ -339,7 +339,7 @@ cllm_status enqueue_iteration(cllm_ctx *c, const IterShape &sh, int32_t *out_dev
     hipEvent_t e0, e1;
     const RowsRef rr{c->tab, c->rows, c->cap};
 
-    EmbedParams ep{c->embed, c->X, c->ssq, c->An, c->g_attn[0], c->d, rr};
+    EmbedParams ep{c->embed, c->X, c->ssq, c->An, c->g_attn[0], c->d, rr, prompt_gemm ? c->sinv : nullptr, c->cfg.rms_eps};
     timing_events(c, CLLM_KT_EMBED, rg, &e0, &e1);
     HIPCHK(c, launch_embed(c->bf16, sh.R, ep, s, e0, e1));
 
@@ -423,6 +423,7 @@ cllm_status enqueue_iteration(cllm_ctx *c, const IterShape &sh, int32_t *out_dev
         o.A = c->O;
         o.lda = c->d;
         o.gain = c->g_ffn[l];
+        if (prompt_gemm) o.ssq_out = nullptr;  // prompt products read the row factors
         timing_events(c, CLLM_KT_GEMM_O, rg, &e0, &e1);
         HIPCHK(c, prompt_gemm ? launch_gemm_prompt(GEMM_O, sh.R, o, s, e0, e1)
                               : launch_gemm(GEMM_O, c->bf16, rg, row_tiles, o, s, e0, e1));
@@ -445,6 +446,7 @@ cllm_status enqueue_iteration(cllm_ctx *c, const IterShape &sh, int32_t *out_dev
         dn.A = c->Hb;
         dn.lda = c->Fp;
         dn.gain = l + 1 < c->NL ? c->g_attn[l + 1] : c->g_final;
+        if (prompt_gemm && l + 1 < c->NL) dn.ssq_out = nullptr;  // the LM head after a prompt reads the sums
         timing_events(c, CLLM_KT_GEMM_DOWN, rg, &e0, &e1);
         HIPCHK(c, prompt_gemm ? launch_gemm_prompt(GEMM_DOWN, sh.R, dn, s, e0, e1)
                               : launch_gemm(GEMM_DOWN, c->bf16, rg, row_tiles, dn, s, e0, e1));

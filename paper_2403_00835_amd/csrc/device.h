@@ -11,6 +11,7 @@ typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 typedef __attribute__((ext_vector_type(2))) unsigned int u32x2;
 
 constexpr int kWave = 64;
+constexpr int kCUs = 256;          // compute units of an MI355X
 constexpr int kMaxBlock = 64;      // largest Jacobi block (rows per iteration)
 constexpr int kMaxRows = 64;       // rows of one GEMM row tile; activation buffers hold a multiple
 constexpr int kMaxSeqs = 64;       // sequences of one batched iteration
@@ -108,6 +109,31 @@ __device__ __forceinline__ void put_act(typename PrecT<P>::T *base, size_t plane
     }
 }
 
+// Store eight consecutive values (columns a multiple of 8 on) at element i of a bf16 activation
+// operand, one 16-byte vector per plane.
+__device__ __forceinline__ void put_act8(uint16_t *base, size_t plane, size_t i, const float *x) {
+    alignas(16) uint16_t hi[8], lo[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        hi[e] = f2bf(x[e]);
+        lo[e] = f2bf(x[e] - bf2f(hi[e]));
+    }
+    *reinterpret_cast<u32x4 *>(base + i) = *reinterpret_cast<const u32x4 *>(hi);
+    *reinterpret_cast<u32x4 *>(base + plane + i) = *reinterpret_cast<const u32x4 *>(lo);
+}
+
+// The RMSNorm factor 1/sqrt(sum / K + eps) of one row from its workgroup's partial sums of squares
+// (at most four waves): a fixed tree over each wave's lanes, then the waves in order. s_sum: LDS.
+__device__ __forceinline__ float row_factor_of_block(float sum, int K, float eps, float (&s_sum)[4]) {
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) sum += __shfl_xor(sum, off);
+    if ((threadIdx.x & 63) == 0) s_sum[threadIdx.x >> 6] = sum;
+    __syncthreads();
+    float tot = 0.0f;
+    for (int w = 0; w < (int)(blockDim.x + 63) / 64; ++w) tot += s_sum[w];
+    return 1.0f / sqrtf(tot / (float)K + eps);
+}
+
 // Makes wave-uniform values available at this point. Kernel prologues list here every
 // parameter (and row-table field) their first loads need, so those are requested in one round
 // trip; left to itself the compiler requests each one next to its first use, behind the
@@ -124,6 +150,14 @@ __device__ __forceinline__ void wait_vm() {
     static_assert(N >= 0 && N < 64, "vmcnt holds 6 bits");
     // s_waitcnt with vmcnt = N (bits 3:0 and 15:14) and the other counters at their maxima
     __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
+}
+
+// The same, and every LDS access of this wave is complete.
+template <int N>
+__device__ __forceinline__ void wait_vm_lds() {
+    static_assert(N >= 0 && N < 64, "vmcnt holds 6 bits");
+    asm volatile("" ::: "memory");  // LDS reads stay before the wait
+    __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | ((N >> 4) << 14));
 }
 
 // Workgroup barrier without the compiler's memory fence (which would wait for every outstanding

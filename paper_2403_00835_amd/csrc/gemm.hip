@@ -395,47 +395,73 @@ __global__ __launch_bounds__(W * kWave) void gemm_kernel(GemmParams p) {
 // operands, for workgroup tiles of 16 RG rows x 16 NT columns. The 8 waves form a WM x (8 / WM)
 // grid over the tile and each accumulates its sub-tile over every k-step in order (one MFMA per
 // plane, hi then lo). The operands of a k-step (2 RG activation blocks and NT weight tiles of
-// 1 KiB each) are loaded once per workgroup from global memory straight into LDS (LDS DMA: no
-// register round trip, no LDS write instructions), into a ring of NB buffers NB - 1 k-steps
-// ahead, with a small LDS footprint so that two or three workgroups share a CU and hide each
-// other's latency. A k-step's blocks are complete once this wave's DMA count has dropped to the
-// later k-steps' loads (explicit vmcnt wait) and every wave has passed a barrier; the barrier is
-// issued without the compiler's LDS fence (which would wait for every outstanding DMA), with
-// compiler-only fences so no LDS access moves across it. The buffer a k-step refills was last
-// read in the previous k-step, before that barrier. A row's reduction order depends only on K
-// (and on the fixed K ranges of a split launch), never on the rows of a pass, so every prompt
-// row gets the same values whatever the chunk size; the order differs from gemm_kernel's (which
-// keeps eight k-step classes so decode rows are exact across row counts), so prompt rows always
-// take this kernel. Epilogues and the RMSNorm row factor are gemm_kernel's.
+// 1 KiB each) are loaded once per workgroup from global memory straight into LDS (LDS DMA), into a
+// ring of NB buffers.
+//
+// What bounds it: a CU keeps a fixed amount of loads in flight, so it pulls 65-70 GB/s of operand
+// bytes here whatever the ring's depth (4 or 5 buffers the same, 3 too few), and its LDS reads
+// compete with the MFMAs; both fall with larger tiles. Hence one workgroup per CU with the largest
+// tile that still gives every CU one (128 x 384 for gate/up: 160 KiB of LDS, 232 workgroups at
+// 512 rows), not several small ones. Each wave holds two sets of operand registers: while
+// the MFMAs of a k-step run, the next k-step's operands are read from LDS between them, so neither
+// waits for the other, and the barrier of a k-step finds its operands already in registers.
+// Measured at the LLaMA-2-7B shape, 512 rows, random operands, against the former kernel (64 x 256
+// and 64 x 128 tiles, two or three workgroups per CU, the operands of a k-step read, waited for
+// and then multiplied): gate/up 179 -> 150 us, QKV 119 -> 91, down (with its reduction) 102 -> 91,
+// O 50 -> 50 (1.0-1.2 PFLOP/s of MFMA work). Prefetching a later k-step into L2 from the same waves
+// was slower (194 us for gate/up): the prefetches wait in the same in-order queue.
+//
+// Ring: at k-step s a wave waits until its DMA blocks of k-step s + 1 have landed and its own LDS
+// reads are complete, passes the barrier, issues k-step s + NB - 1 into the buffer of k-step s - 1
+// and reads k-step s + 1. Every wave read buffer s - 1 before it computed k-step s - 1, so no
+// reader is left when it is refilled. The barrier is issued without the compiler's LDS fence (which
+// would wait for every outstanding DMA), with compiler-only fences so no LDS access moves across it.
+//
+// A row's reduction order depends only on K (and on the fixed K ranges of a split launch), never
+// on the tile or the rows of a pass, so every prompt row gets the same values whatever the chunk
+// size; the order differs from gemm_kernel's (which keeps eight k-step classes so decode rows are
+// exact across row counts), so prompt rows always take this kernel. The RMSNorm row factors of
+// prompt rows are computed once, by the kernel that writes the rows (embed_kernel,
+// prompt_reduce_kernel), instead of by every workgroup from the sums of squares (3.5-4.5 us of
+// each launch). Epilogues: through LDS into 16-byte vectors of the output's layout.
 // ------------------------------------------------------------------------------------------
-template <int NT, int RG, int EP, int NB>
-__host__ __device__ constexpr int prompt_dma_lds_floats() {
-    constexpr int ROWS = 16 * RG, COLS = 16 * NT, BLK = 2 * RG + NT;
-    constexpr int stage = NB * BLK * kWave * 4;
-    constexpr int after = (EP == E_RESID ? ROWS * COLS : 0) + ROWS * (COLS + 1);
-    return (stage > after ? stage : after) + ROWS;
+// floats per row of a wave's epilogue block (16-byte rows, spread over the banks)
+template <int NT, int WM, int EP>
+__host__ __device__ constexpr int prompt_row_floats() {
+    return (EP == E_SWIGLU ? 8 : 16) * (NT / (kGemmWaves / WM)) + 4;
+}
+template <int NT, int RG, int WM, int EP, int NB>
+__host__ __device__ constexpr int prompt_lds_bytes() {
+    constexpr int stage = NB * (2 * RG + NT) * kTileBytes;
+    constexpr int after = (kGemmWaves * (16 * RG / WM) * prompt_row_floats<NT, WM, EP>() + 16 * RG) * 4;
+    return stage > after ? stage : after;
 }
 
 template <int NT, int RG, int WM, int EP, int NB>
-__global__ __launch_bounds__(kGemmWaves * kWave) void gemm_prompt_dma_kernel(GemmParams p) {
+__global__ __launch_bounds__(kGemmWaves * kWave, 2) void gemm_prompt_kernel(GemmParams p) {
     constexpr Prec P = Prec::BF16;
     constexpr int W = kGemmWaves, WN = W / WM, RGW = RG / WM, NTW = NT / WN;
-    constexpr int BLK = 2 * RG + NT, NLW = BLK / W;  // 1 KiB blocks per k-step, DMA loads per wave
-    static_assert(RG % WM == 0 && NT % WN == 0 && BLK % W == 0 && NB >= 3, "tile split, ring depth");
-    constexpr bool ROWSCALE = EP != E_RESID && EP != E_LOGITS;  // the product follows an RMSNorm
-    constexpr int ROWS = 16 * RG, COLS = 16 * NT;
+    constexpr int BLK = 2 * RG + NT, NLW = (BLK + W - 1) / W;  // 1 KiB blocks per k-step, DMA loads per wave
+    static_assert(RG % WM == 0 && NT % WN == 0 && NB >= 4, "tile split, ring depth");
+    static_assert(EP == E_QKV || EP == E_SWIGLU || EP == E_LOGITS, "the prompt products' epilogues");
+    static_assert(EP != E_SWIGLU || NTW % 2 == 0, "a wave holds whole (gate, up) tile pairs");
+    static_assert(kWave % (16 * RGW) == 0, "QKV epilogue: a lane serves one row");
+    constexpr bool ROWSCALE = EP != E_LOGITS;  // the product follows an RMSNorm
+    constexpr int ROWS = 16 * RG, WROWS = 16 * RGW;
     // Workgroup L runs on XCD L % 8 (round-robin dispatch). Column group cg belongs to XCD cg % 8,
     // and each XCD takes its column groups in turn with their row tiles consecutively, so the row
     // tiles of a column group run together and read its weights once from HBM into that XCD's L2.
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
     const int wg = (slot / p.row_tiles) * 8 + xcd, row0 = (slot % p.row_tiles) * ROWS;
-    request_together(p.W, p.A, p.ssq, p.Ks, p.cols, p.lda, p.rr.cap, p.T, p.n_wg);
+    request_together(p.W, p.A, p.Ks, p.cols, p.lda, p.rr.cap, p.n_wg, p.rr.rows, p.rr.tab, p.sinv);
     const int m = p.rr.tab->R - row0;
     if (m <= 0 || wg >= p.n_wg) return;
     const int rg0 = row0 >> 4, t0 = wg * NT;
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = w / WN, wn = w % WN;
+    const int wrow = wm * WROWS;     // the wave's first row of the tile
+    const bool live = wrow < m;      // a wave whose rows are all past the pass only helps load
     // E_LOGITS with p.kc > 0: grid y takes k-steps [y kc, min((y + 1) kc, Ks)) and writes its
     // partial products to plane y
     int Ks = p.Ks, ks0 = 0;
@@ -446,25 +472,37 @@ __global__ __launch_bounds__(kGemmWaves * kWave) void gemm_prompt_dma_kernel(Gem
             p.Zout += (size_t)blockIdx.y * p.zstride;
         }
     }
-
     extern __shared__ float smem[];
     u32x4 *s_stage = reinterpret_cast<u32x4 *>(smem);  // [NB][BLK][64] during the main loop
-    float *s_red = smem;                               // then epilogue scratch (E_RESID) ...
-    float *s_tile = smem + (EP == E_RESID ? ROWS * COLS : 0);  // ... and the output tile
-    float *s_inv = smem + prompt_dma_lds_floats<NT, RG, EP, NB>() - ROWS;  // row factors (apart)
 
-    f32x4 sq_pre[2];
-    if constexpr (ROWSCALE) row_factor_preload<W>(p, row0, tid, sq_pre);
+    // what the epilogue needs of the rows, requested before the main loop: the row factors (one
+    // row per thread) and, for QKV, the position and slot of the lane's row
+    float inv = 0.0f;
+    if constexpr (ROWSCALE) {
+        if (tid < ROWS) inv = p.sinv[row0 + tid];  // row0 + tid < row capacity (launcher)
+    }
+    const int erow = lane % WROWS;  // QKV: the lane's row of the wave's block
+    int epos = 0, eslot = 0;
+    if constexpr (EP == E_QKV) {
+        if (wrow + erow < m) {
+            const RowInfo ri = p.rr.rows[row0 + wrow + erow];
+            epos = ri.pos;
+            eslot = p.rr.tab->seq[ri.b];
+        }
+    }
 
     // This wave's blocks b = w + i W of every k-step: block b < 2 RG is activation plane b / RG,
-    // row group b % RG; block 2 RG + j is weight tile t0 + j (clamped). A k-step advances an
+    // row group b % RG; block 2 RG + j is weight tile t0 + j (clamped; its columns are never
+    // written). Where the last round has no block for a wave, it loads the last block again into
+    // its place, so every wave has the same number of loads in flight. A k-step advances an
     // activation block by 64 vectors and a weight block by one k-step of tiles.
     const int tiles = p.cols >> 4, ks_a = p.lda / PrecT<P>::KSTEP;
     const u32x4 *src[NLW];
-    int adv[NLW];
+    int adv[NLW], dst[NLW];
 #pragma unroll
     for (int i = 0; i < NLW; ++i) {
-        const int b = w + i * W;
+        const int b = min(w + i * W, BLK - 1);
+        dst[i] = b;
         if (b < 2 * RG) {
             const uint16_t *A = reinterpret_cast<const uint16_t *>(p.A) + (b / RG) * act_plane(p.rr.cap, p.lda);
             src[i] = reinterpret_cast<const u32x4 *>(A + (size_t)(rg0 + b % RG) * ks_a * kWave * 8) + lane;
@@ -475,62 +513,184 @@ __global__ __launch_bounds__(kGemmWaves * kWave) void gemm_prompt_dma_kernel(Gem
         }
         src[i] += (size_t)ks0 * adv[i];  // the first k-step of this workgroup's K range
     }
-    // k-step s into ring buffer s % NB; past the last k-step a harmless reload of it
-    auto issue = [&](int s) {
+    // k-step s into ring buffer buf; past the last k-step a harmless reload of it
+    auto issue = [&](int s, int buf) {
         const size_t ss = (size_t)min(s, Ks - 1);
-        u32x4 *buf = s_stage + (size_t)(s % NB) * BLK * kWave;
+        u32x4 *bb = s_stage + (size_t)buf * BLK * kWave;
 #pragma unroll
         for (int i = 0; i < NLW; ++i)
             __builtin_amdgcn_global_load_lds(static_cast<const void *>(src[i] + ss * adv[i]),
-                                             (__attribute__((address_space(3))) void *)(buf + (size_t)(w + i * W) * kWave),
-                                             16, 0, 0);
+                                             (__attribute__((address_space(3))) void *)(bb + (size_t)dst[i] * kWave), 16,
+                                             0, 0);
     };
+#pragma unroll
+    for (int q = 0; q < NB - 1; ++q) issue(q, q);
+
     f32x4 acc[RGW][NTW];
 #pragma unroll
     for (int r = 0; r < RGW; ++r)
 #pragma unroll
         for (int j = 0; j < NTW; ++j) acc[r][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-
+    u32x4 a[2][2][RGW], b[2][NTW];  // two sets: the k-step being computed, the next one
+    auto read_operands = [&](auto set, int buf) {
+        constexpr int st = decltype(set)::value;
+        const u32x4 *bp = s_stage + (size_t)buf * BLK * kWave + lane;
 #pragma unroll
-    for (int q = 0; q < NB - 1; ++q) issue(q);
-    for (int s = 0; s < Ks; ++s) {
-        wait_vm<(NB - 2) * NLW>();  // this wave's blocks of k-step s have landed
-        barrier_no_fence();         // every wave's; buffer (s - 1) % NB has no reader left
-        issue(s + NB - 1);
-        const u32x4 *bp = s_stage + (size_t)(s % NB) * BLK * kWave + lane;
-        u32x4 a[2][RGW], b[NTW];
+        for (int j = 0; j < NTW; ++j) b[st][j] = bp[(2 * RG + wn * NTW + j) * kWave];
 #pragma unroll
         for (int pl = 0; pl < 2; ++pl)
 #pragma unroll
-            for (int r = 0; r < RGW; ++r) a[pl][r] = bp[(pl * RG + wm * RGW + r) * kWave];
+            for (int r = 0; r < RGW; ++r) a[st][pl][r] = bp[(pl * RG + wm * RGW + r) * kWave];
+    };
+    int rbuf = 1, ibuf = NB - 1;  // ring buffers of k-steps s + 1 and s + NB - 1
+    auto step = [&](auto set, int s) {
+        constexpr int st = decltype(set)::value;
+        wait_vm_lds<(NB - 3) * NLW>();  // this wave's blocks of k-step s + 1 have landed
+        barrier_no_fence();             // every wave's; buffer ibuf has no reader left
+        issue(s + NB - 1, ibuf);
+        if (live) {
+            read_operands(std::integral_constant<int, st ^ 1>{}, rbuf);
 #pragma unroll
-        for (int j = 0; j < NTW; ++j) b[j] = bp[(2 * RG + wn * NTW + j) * kWave];
+            for (int pl = 0; pl < 2; ++pl)
 #pragma unroll
-        for (int pl = 0; pl < 2; ++pl)
+                for (int r = 0; r < RGW; ++r)
 #pragma unroll
-            for (int r = 0; r < RGW; ++r)
+                    for (int j = 0; j < NTW; ++j) acc[r][j] = mfma_kstep<P>(a[st][pl][r], b[st][j], acc[r][j]);
+            // schedule: one LDS read after every few MFMAs
+            constexpr int reads = 2 * RGW + NTW, mfmas = 2 * RGW * NTW, per = mfmas >= reads ? mfmas / reads : 1;
 #pragma unroll
-                for (int j = 0; j < NTW; ++j) acc[r][j] = mfma_kstep<P>(a[pl][r], b[j], acc[r][j]);
+            for (int i = 0; i < reads; ++i) {
+                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // LDS read
+                __builtin_amdgcn_sched_group_barrier(0x008, per, 0);  // MFMA
+            }
+            __builtin_amdgcn_sched_group_barrier(0x008, mfmas, 0);
+        }
+        rbuf = rbuf == NB - 1 ? 0 : rbuf + 1;
+        ibuf = ibuf == NB - 1 ? 0 : ibuf + 1;
+    };
+    constexpr std::integral_constant<int, 0> set0{};
+    constexpr std::integral_constant<int, 1> set1{};
+    wait_vm<(NB - 2) * NLW>();  // this wave's blocks of k-step 0
+    barrier_no_fence();
+    if (live) read_operands(set0, 0);
+    int s = 0;
+    for (; s + 2 <= Ks; s += 2) {
+        step(set0, s);
+        step(set1, s + 1);
     }
+    if (s < Ks) step(set0, s);
     wait_vm<0>();  // the trailing reloads have landed before the buffers are reused
     __syncthreads();
 
-    if constexpr (ROWSCALE) row_factor_reduce<W, ROWS>(p, row0, tid, sq_pre, s_inv);
-    __syncthreads();
-    // C layout of a 16 x 16 tile: lane l, register v -> row 4 (l / 16) + v, column l % 16
+    // The wave's outputs into its LDS block (C layout of a 16 x 16 tile: lane l, register v -> row
+    // 4 (l / 16) + v, column l % 16), then out as vectors.
+    constexpr int LDR = prompt_row_floats<NT, WM, EP>();
+    float *s_w = smem + (size_t)w * WROWS * LDR;
+    float *s_inv = smem + (size_t)W * WROWS * LDR;
+    if constexpr (ROWSCALE) {
+        if (tid < ROWS) s_inv[tid] = inv;
+        __syncthreads();
+    }
+    if (!live) return;
+    const int c16 = lane & 15, r4 = 4 * (lane >> 4);
 #pragma unroll
-    for (int r = 0; r < RGW; ++r)
+    for (int r = 0; r < RGW; ++r) {
+        f32x4 iv = f32x4{1.f, 1.f, 1.f, 1.f};
+        if constexpr (ROWSCALE) iv = *reinterpret_cast<const f32x4 *>(s_inv + wrow + 16 * r + r4);
+        if constexpr (EP == E_SWIGLU) {
 #pragma unroll
-        for (int j = 0; j < NTW; ++j)
+            for (int j = 0; j < NTW; j += 2)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int row = 16 * (wm * RGW + r) + 4 * (lane >> 4) + v;
-                float x = acc[r][j][v];
-                if constexpr (ROWSCALE) x *= s_inv[row];
-                s_tile[row * (COLS + 1) + 16 * (wn * NTW + j) + (lane & 15)] = x;
+                for (int v = 0; v < 4; ++v) {
+                    const float g = acc[r][j][v] * iv[v], u = acc[r][j + 1][v] * iv[v];
+                    s_w[(16 * r + r4 + v) * LDR + 8 * j + c16] = silu(g) * u;
+                }
+        } else {
+#pragma unroll
+            for (int j = 0; j < NTW; ++j)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    float x = acc[r][j][v];
+                    if constexpr (ROWSCALE) x *= iv[v];
+                    s_w[(16 * r + r4 + v) * LDR + 16 * j + c16] = x;
+                }
+        }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");  // the wave reads back its own block only
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    if constexpr (EP == E_SWIGLU) {
+        uint16_t *H = reinterpret_cast<uint16_t *>(p.H);
+#pragma unroll 2
+        for (int i = lane; i < WROWS * NTW; i += kWave) {  // NTW vectors of 8 features per row
+            const int row = i % WROWS, q = i / WROWS;
+            const int t = t0 + wn * NTW + (q & ~1);  // the gate tile of the pair
+            if (wrow + row >= m || t >= tiles) continue;
+            alignas(16) float x[8];
+            *reinterpret_cast<f32x4 *>(x) = *reinterpret_cast<const f32x4 *>(s_w + row * LDR + 8 * q);
+            *reinterpret_cast<f32x4 *>(x + 4) = *reinterpret_cast<const f32x4 *>(s_w + row * LDR + 8 * q + 4);
+            put_act8(H, act_plane(p.rr.cap, p.Fp), act_idx<P>(row0 + wrow + row, t * 8 + 8 * (q & 1), p.Fp), x);
+        }
+    } else if constexpr (EP == E_QKV) {
+        // One tile of the lane's row at a time: 8 dims of a head and their 8 rotate-half partners.
+        const int hd = p.hd, d = p.d, h2 = hd >> 1;
+        if (wrow + erow >= m) return;
+        const size_t kvs = (size_t)eslot * p.kv_seq;
+        for (int j = lane / WROWS; j < NTW; j += kWave / WROWS) {
+            const int R0 = (t0 + wn * NTW + j) * 16;
+            if (R0 >= p.cols) break;
+            const int sec = R0 / d, within = R0 % d, head = within / hd, dim = (within % hd) >> 1;
+            const size_t kvo = kvs + (size_t)head * p.ctx_alloc * hd;
+            alignas(16) float x[16];
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                *reinterpret_cast<f32x4 *>(x + 4 * q) = *reinterpret_cast<const f32x4 *>(s_w + erow * LDR + 16 * j + 4 * q);
+            if (sec < 2) {
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    const f32x4 c = *reinterpret_cast<const f32x4 *>(p.rcos + (size_t)epos * h2 + dim + 4 * q);
+                    const f32x4 sn = *reinterpret_cast<const f32x4 *>(p.rsin + (size_t)epos * h2 + dim + 4 * q);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float u = x[4 * q + e], y = x[8 + 4 * q + e];
+                        x[4 * q + e] = u * c[e] - y * sn[e];
+                        x[8 + 4 * q + e] = y * c[e] + u * sn[e];
+                    }
+                }
             }
-    __syncthreads();
-    gemm_epilogue<P, NT, RG, EP, W>(p, s_tile, s_red, row0, m, wg, tid, lane, w);
+            if (sec == 0) {
+                uint16_t *Q = reinterpret_cast<uint16_t *>(p.Q);
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+                    put_act8(Q, act_plane(p.rr.cap, d), act_idx<P>(row0 + wrow + erow, head * hd + h * h2 + dim, d), x + 8 * h);
+            } else {  // cached keys and values are rounded to the cache dtype
+                alignas(16) uint16_t y[16];
+#pragma unroll
+                for (int e = 0; e < 16; ++e) y[e] = f2bf(x[e]);
+                if (sec == 1) {
+                    uint16_t *Kc = reinterpret_cast<uint16_t *>(p.Kc) + kvo;
+#pragma unroll
+                    for (int h = 0; h < 2; ++h)
+                        *reinterpret_cast<u32x4 *>(Kc + kcache_idx<P>(epos, h * h2 + dim, hd)) =
+                            *reinterpret_cast<const u32x4 *>(y + 8 * h);
+                } else {
+                    uint16_t *Vt = reinterpret_cast<uint16_t *>(p.Vt) + kvo;
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) Vt[vcache_idx<P>(epos, (e >> 3) * h2 + dim + (e & 7), hd)] = y[e];
+                }
+            }
+        }
+    } else {  // E_LOGITS: fp32 rows
+        constexpr int VPR = 4 * NTW;
+#pragma unroll 4
+        for (int i = lane; i < WROWS * VPR; i += kWave) {
+            const int row = i / VPR, q = i % VPR;
+            const int c = (t0 + wn * NTW) * 16 + 4 * q;
+            if (wrow + row < m && c < p.cols)
+                *reinterpret_cast<f32x4 *>(p.Zout + (size_t)(row0 + wrow + row) * p.ldz + c) =
+                    *reinterpret_cast<const f32x4 *>(s_w + row * LDR + 4 * q);
+        }
+    }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1031,46 +1191,154 @@ static hipError_t launch_split_t(const GemmParams &p, int row_tiles, hipStream_t
     return hipGetLastError();
 }
 
-template <int NT, int RG, int WM, int EP, int NB>
-static hipError_t launch_prompt_dma(const GemmParams &p, int rows, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-    constexpr int ROWS = 16 * RG, COLS = 16 * NT;
-    const size_t lds = (size_t)prompt_dma_lds_floats<NT, RG, EP, NB>() * sizeof(float);
-    if (rows < 1 || rows > p.rr.cap || p.rr.cap % ROWS != 0 || p.lda % 32 != 0 || p.cols % 16 != 0)
-        return hipErrorInvalidValue;
-    GemmParams q = p;
-    q.n_wg = (p.cols + COLS - 1) / COLS;
-    q.row_tiles = (rows + ROWS - 1) / ROWS;
-    const dim3 grid((unsigned)((q.n_wg + 7) / 8 * 8 * q.row_tiles));  // column groups padded to 8 XCDs
-    auto kern = gemm_prompt_dma_kernel<NT, RG, WM, EP, NB>;
-    if (e0 || e1)
-        hipExtLaunchKernelGGL(kern, grid, dim3(kGemmWaves * kWave), lds, s, e0, e1, 0, q);
+// The residual epilogue of a prompt product: the fp32 partial planes of its NS K ranges summed in
+// range order, X += Y, the next RMSNorm operand X (.) gain, the row's RMSNorm factor and, where
+// asked for, the per-16-column sums of squares. One workgroup per row (its sum of squares needs no
+// second pass): each thread takes the row's 8-column vectors tid, tid + threads, ...; the threads'
+// sums are added in a fixed tree (lanes, then waves in order), so the factor depends on the row
+// and the model's width only.
+template <int NS>
+__global__ __launch_bounds__(256) void prompt_reduce_kernel(GemmParams p, size_t zstride) {
+    constexpr Prec P = Prec::BF16;
+    const int row = blockIdx.x, tid = threadIdx.x;
+    request_together(p.rr.tab, p.part, p.Xout, p.gain, p.An, p.ldx, p.cols, p.rr.cap);
+    if (row >= p.rr.tab->R) return;
+    __shared__ float s_sum[4];
+    float ss_row = 0.0f;
+    for (int g = tid; g < p.cols / 8; g += blockDim.x) {
+        const int c0 = 8 * g;
+        const size_t o = (size_t)row * p.ldx + c0;
+        f32x4 q[NS][2], xv[2], gv[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+#pragma unroll
+            for (int z = 0; z < NS; ++z) q[z][h] = *reinterpret_cast<const f32x4 *>(p.part + z * zstride + o + 4 * h);
+            xv[h] = *reinterpret_cast<const f32x4 *>(p.Xout + o + 4 * h);
+            gv[h] = *reinterpret_cast<const f32x4 *>(p.gain + c0 + 4 * h);
+        }
+        alignas(16) float x[8], a[8];
+        float ss = 0.0f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            float y = q[0][e >> 2][e & 3];
+            if constexpr (NS > 1) y += q[1][e >> 2][e & 3];
+            if constexpr (NS == 3) y += q[2][e >> 2][e & 3];
+            if constexpr (NS == 4) y += q[2][e >> 2][e & 3] + q[3][e >> 2][e & 3];
+            x[e] = xv[e >> 2][e & 3] + y;
+            ss += x[e] * x[e];
+            a[e] = x[e] * gv[e >> 2][e & 3];
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+            *reinterpret_cast<f32x4 *>(p.Xout + o + 4 * h) = *reinterpret_cast<const f32x4 *>(x + 4 * h);
+        put_act8(reinterpret_cast<uint16_t *>(p.An), act_plane(p.rr.cap, p.ldx), act_idx<P>(row, c0, p.ldx), a);
+        if (p.ssq_out) {  // a 16-column tile is two consecutive threads'
+            const float other = __shfl_xor(ss, 1);
+            if ((g & 1) == 0) p.ssq_out[(size_t)row * p.T + (g >> 1)] = ss + other;
+        }
+        ss_row += ss;
+    }
+    const float inv = row_factor_of_block(ss_row, p.K, p.eps, s_sum);
+    if (tid == 0) p.sinv[row] = inv;
+}
+
+static hipError_t launch_prompt_reduce(const GemmParams &p, int nsplit, size_t zstride, int rows, hipStream_t s,
+                                       hipEvent_t e1) {
+    if (!p.sinv || !p.gain || p.cols % 16 != 0) return hipErrorInvalidValue;
+    // whole waves, at most 256 threads: one 8-column vector each where the width allows it
+    const int threads = std::min(256, (p.cols / 8 + kWave - 1) / kWave * kWave);
+    auto kern = nsplit == 1 ? prompt_reduce_kernel<1> : nsplit == 2 ? prompt_reduce_kernel<2>
+                : nsplit == 3 ? prompt_reduce_kernel<3> : prompt_reduce_kernel<4>;
+    if (e1)
+        hipExtLaunchKernelGGL(kern, dim3(rows), dim3(threads), 0, s, nullptr, e1, 0, p, zstride);
     else
-        hipLaunchKernelGGL(kern, grid, dim3(kGemmWaves * kWave), lds, s, q);
+        hipLaunchKernelGGL(kern, dim3(rows), dim3(threads), 0, s, p, zstride);
     return hipGetLastError();
 }
 
+// The prompt product over `rows` rows; NS > 0 (E_LOGITS): as NS K ranges into the fp32 partial
+// planes of p.part, then prompt_reduce_kernel.
+template <int NT, int RG, int WM, int EP, int NB, int NS = 0>
+static hipError_t launch_prompt_t(const GemmParams &p, int rows, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+    constexpr int ROWS = 16 * RG, COLS = 16 * NT;
+    constexpr size_t lds = (size_t)prompt_lds_bytes<NT, RG, WM, EP, NB>();
+    static_assert(lds <= 160 * 1024, "the LDS of a CU");
+    static_assert((NS > 0) == (EP == E_LOGITS) && NS <= kDownSplits, "K ranges");
+    if (rows < 1 || rows > p.rr.cap || p.rr.cap % ROWS != 0 || p.lda % 32 != 0 || p.cols % 16 != 0 || p.Ks < 1)
+        return hipErrorInvalidValue;
+    if (EP == E_LOGITS ? (!p.part || p.ldx < p.cols || p.ldx % 8 != 0) : !p.sinv) return hipErrorInvalidValue;
+    if (EP == E_QKV && (p.hd % 16 != 0 || p.d % p.hd != 0)) return hipErrorInvalidValue;
+    GemmParams q = p;
+    int nsplit = 1;
+    if constexpr (NS > 0) {
+        q.kc = (p.Ks + NS - 1) / NS;
+        nsplit = (p.Ks + q.kc - 1) / q.kc;
+        q.Zout = p.part;
+        q.ldz = p.ldx;
+        q.zstride = (size_t)p.rr.cap * p.ldx;
+    }
+    q.n_wg = (p.cols + COLS - 1) / COLS;
+    q.row_tiles = (rows + ROWS - 1) / ROWS;
+    const dim3 grid((unsigned)((q.n_wg + 7) / 8 * 8 * q.row_tiles), (unsigned)nsplit);  // column groups padded to 8 XCDs
+    auto kern = gemm_prompt_kernel<NT, RG, WM, EP, NB>;
+    hipEvent_t end = NS > 0 ? nullptr : e1;
+    if (e0 || end)
+        hipExtLaunchKernelGGL(kern, grid, dim3(kGemmWaves * kWave), lds, s, e0, end, 0, q);
+    else
+        hipLaunchKernelGGL(kern, grid, dim3(kGemmWaves * kWave), lds, s, q);
+    hipError_t err = hipGetLastError();
+    if (err != hipSuccess || NS == 0) return err;
+    return launch_prompt_reduce(p, nsplit, q.zstride, rows, s, e1);
+}
 
-template <int NT, int RG, int WM, int NB, int NS>
-static hipError_t launch_prompt_ksplit(const GemmParams &p, int rows, hipStream_t s, hipEvent_t e0, hipEvent_t e1);
+// Workgroups of a prompt product in 16 RG x 16 NT tiles over `splits` K ranges.
+template <int NT, int RG>
+static bool prompt_fits(const GemmParams &p, int rows, int splits) {
+    return (p.cols + 16 * NT - 1) / (16 * NT) * ((rows + 16 * RG - 1) / (16 * RG)) * splits <= kCUs;
+}
 
+constexpr int kPromptSplitsO = 2, kPromptSplitsDown = 4;
+
+template <int NS>
+static hipError_t launch_prompt_resid(const GemmParams &p, int rows, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+    if (prompt_fits<4, 4>(p, rows, NS)) return launch_prompt_t<4, 4, 2, E_LOGITS, 5, NS>(p, rows, s, e0, e1);
+    if (prompt_fits<8, 4>(p, rows, NS)) return launch_prompt_t<8, 4, 2, E_LOGITS, 5, NS>(p, rows, s, e0, e1);
+    if (prompt_fits<8, 8>(p, rows, NS)) return launch_prompt_t<8, 8, 2, E_LOGITS, 5, NS>(p, rows, s, e0, e1);
+    return launch_prompt_t<16, 8, 2, E_LOGITS, 4, NS>(p, rows, s, e0, e1);
+}
+
+// Tile rule: the smallest tile whose workgroups still fit the chip in one round (one workgroup per
+// CU; they are too large to share one), the largest tile if none does. A second, partly filled
+// round costs as much as a full one, and a larger tile than needed leaves CUs idle while its
+// workgroups take longer. Measured at the LLaMA-2-7B shape, us per launch (O and down with their
+// reduction), the tile taken first, then the next smaller and the next larger one:
+//   gate/up 512 rows: 128x384 160 (128x192 171); 256: 128x192 87 (64x192 102, 128x384 126);
+//           128: 64x192 55 (64x128 76, 128x192 71); 64: 64x128 42 (64x192 52)
+//   QKV     512: 128x192 91 (64x192 108); 256: 64x192 53 (64x96 66, 128x192 79);
+//           128: 64x96 39 (64x64 60, 64x192 50); 64: 64x64 34 (64x96 38)
+//   O       512: 128x128 50 (64x128 50); 256: 64x128 32 (64x64 38, 128x128 41); 64: 64x64 24 (64x128 27)
+//   down    512: 128x256 91 (128x128 105); 256: 128x128 55 (64x128 62, 128x256 72);
+//           128: 64x128 39 (64x64 52, 128x128 49); 64: 64x64 32 (64x128 35)
+// O and down split K into 2 and 4 ranges (fixed: they are part of a row's reduction order), which
+// gives their 4096 columns as many workgroups at 512 rows as the other products have.
 hipError_t launch_gemm_prompt(GemmKind kind, int rows, const GemmParams &p, hipStream_t s, hipEvent_t e0,
                               hipEvent_t e1) {
     switch (kind) {
-    // measured at the LLaMA-2-7B shape, 512 rows, random operands: QKV and gate/up take the LDS-DMA
-    // kernel with three buffers (64 x 128 tiles for QKV: 114 us, LDS-staged 64 x 256: 167 us;
-    // 64 x 256 for gate/up: 177-199 us, LDS-staged: 245 us). O and down, whose 4096 columns give
-    // one 64 x 128 workgroup per CU at 512 rows, take the DMA kernel over fixed K ranges and the
-    // reduction: O 64 x 128 tiles and 2 ranges (54.6 us against 56.4 for the LDS-staged kernel;
-    // 37.1 against 52.3 at 256 rows), down 128 x 128 tiles and 4 ranges (103.5 against 116.0;
-    // 61.9 against 102.4 at 256 rows)
     case GEMM_QKV:
-        return launch_prompt_dma<8, 4, 2, E_QKV, 3>(p, rows, s, e0, e1);
+        if (prompt_fits<4, 4>(p, rows, 1)) return launch_prompt_t<4, 4, 2, E_QKV, 5>(p, rows, s, e0, e1);
+        if (prompt_fits<6, 4>(p, rows, 1)) return launch_prompt_t<6, 4, 4, E_QKV, 5>(p, rows, s, e0, e1);
+        if (prompt_fits<12, 4>(p, rows, 1)) return launch_prompt_t<12, 4, 2, E_QKV, 5>(p, rows, s, e0, e1);
+        return launch_prompt_t<12, 8, 2, E_QKV, 5>(p, rows, s, e0, e1);
     case GEMM_GATE_UP:
-        return launch_prompt_dma<16, 4, 2, E_SWIGLU, 3>(p, rows, s, e0, e1);
+        if (prompt_fits<4, 4>(p, rows, 1)) return launch_prompt_t<4, 4, 4, E_SWIGLU, 5>(p, rows, s, e0, e1);
+        if (prompt_fits<8, 4>(p, rows, 1)) return launch_prompt_t<8, 4, 2, E_SWIGLU, 5>(p, rows, s, e0, e1);
+        if (prompt_fits<12, 4>(p, rows, 1)) return launch_prompt_t<12, 4, 4, E_SWIGLU, 5>(p, rows, s, e0, e1);
+        if (prompt_fits<12, 8>(p, rows, 1)) return launch_prompt_t<12, 8, 4, E_SWIGLU, 5>(p, rows, s, e0, e1);
+        return launch_prompt_t<24, 8, 2, E_SWIGLU, 4>(p, rows, s, e0, e1);
     case GEMM_O:  // X += O W_o^T
-        return launch_prompt_ksplit<8, 4, 2, 3, 2>(p, rows, s, e0, e1);
+        return launch_prompt_resid<kPromptSplitsO>(p, rows, s, e0, e1);
     case GEMM_DOWN:  // X += H W_d^T
-        return launch_prompt_ksplit<8, 8, 2, 3, 4>(p, rows, s, e0, e1);
+        return launch_prompt_resid<kPromptSplitsDown>(p, rows, s, e0, e1);
     default:
         return hipErrorInvalidValue;
     }
@@ -1161,46 +1429,6 @@ __global__ __launch_bounds__(kReduceThreads) void down_reduce_kernel(GemmParams 
 #pragma unroll
     for (int k = 0; k < G; ++k) tot += __shfl(ss, base + k);
     if (live && g % G == 0) p.ssq_out[(size_t)row * p.T + g / G] = tot;
-}
-
-// A prompt product with the residual epilogue as NS K ranges through the LDS-DMA kernel (fp32
-// partial planes in p.part), then down_reduce_kernel (partials summed in range order, residual,
-// next RMSNorm operand and its sums of squares).
-template <int NT, int RG, int WM, int NB, int NS>
-static hipError_t launch_prompt_ksplit(const GemmParams &p, int rows, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-    static_assert(NS >= 1 && NS <= kDownSplits, "down_reduce_kernel sums up to kDownSplits partials");
-    constexpr int ROWS = 16 * RG, COLS = 16 * NT;
-    if (!p.part || rows < 1 || rows > p.rr.cap || p.rr.cap % ROWS != 0 || p.lda % 32 != 0 || p.cols % 16 != 0 ||
-        p.ldx < p.cols || p.Ks < NS)
-        return hipErrorInvalidValue;
-    GemmParams q = p;
-    q.kc = (p.Ks + NS - 1) / NS;
-    q.Zout = p.part;
-    q.ldz = p.ldx;
-    q.V = p.cols;
-    q.zstride = (size_t)p.rr.cap * p.ldx;
-    q.n_wg = (p.cols + COLS - 1) / COLS;
-    q.row_tiles = (rows + ROWS - 1) / ROWS;
-    const int nsplit = (p.Ks + q.kc - 1) / q.kc;
-    const size_t lds = (size_t)prompt_dma_lds_floats<NT, RG, E_LOGITS, NB>() * sizeof(float);
-    const dim3 grid((unsigned)((q.n_wg + 7) / 8 * 8 * q.row_tiles), (unsigned)nsplit);
-    auto kern = gemm_prompt_dma_kernel<NT, RG, WM, E_LOGITS, NB>;
-    if (e0)
-        hipExtLaunchKernelGGL(kern, grid, dim3(kGemmWaves * kWave), lds, s, e0, nullptr, 0, q);
-    else
-        hipLaunchKernelGGL(kern, grid, dim3(kGemmWaves * kWave), lds, s, q);
-    hipError_t err = hipGetLastError();
-    if (err != hipSuccess) return err;
-    const int rows_launch = q.row_tiles * ROWS;
-    const size_t n = (size_t)rows_launch * (p.cols / PrecT<Prec::BF16>::VEC);
-    const dim3 grid_r((unsigned)((n + kReduceThreads - 1) / kReduceThreads));
-    if (e1)
-        hipExtLaunchKernelGGL(down_reduce_kernel<Prec::BF16>, grid_r, dim3(kReduceThreads), 0, s, nullptr, e1, 0, p,
-                              nsplit, q.zstride, rows_launch);
-    else
-        hipLaunchKernelGGL(down_reduce_kernel<Prec::BF16>, grid_r, dim3(kReduceThreads), 0, s, p, nsplit, q.zstride,
-                           rows_launch);
-    return hipGetLastError();
 }
 
 // The down product: K split over kDownSplits ranges (fp32 partials in p.part, 64-column

@@ -26,7 +26,7 @@ namespace cllm {
 
 // ------------------------------------------------------------------------------------------
 // Embedding gather: X[i] = E[z_i] (fp32), the operand X[i] (.) g of the first layer's QKV product
-// and the per-16-column sums of squares for its RMSNorm.
+// and the per-16-column sums of squares for its RMSNorm (for prompt rows also the factor itself).
 // ------------------------------------------------------------------------------------------
 template <Prec P>
 __global__ __launch_bounds__(256) void embed_kernel(EmbedParams p) {
@@ -42,6 +42,7 @@ __global__ __launch_bounds__(256) void embed_kernel(EmbedParams p) {
     const T *e = reinterpret_cast<const T *>(p.E) + (size_t)tok * p.d;
     float *x = p.X + (size_t)row * p.d;
     T *an = reinterpret_cast<T *>(p.An);
+    float ss_row = 0.0f;
     for (int t = threadIdx.x; t < p.d / 16; t += blockDim.x) {  // one 16-column tile per thread
         alignas(16) T ev[16];
         alignas(16) T av[PT::PLANES][16];
@@ -71,6 +72,12 @@ __global__ __launch_bounds__(256) void embed_kernel(EmbedParams p) {
                 *reinterpret_cast<u32x4 *>(an + pl * act_plane(p.rr.cap, p.d) + act_idx<P>(row, 16 * t + q * V16, p.d)) =
                     *reinterpret_cast<u32x4 *>(&av[pl][q * V16]);
         p.ssq[(size_t)row * (p.d / 16) + t] = sum;
+        ss_row += sum;
+    }
+    if (p.sinv) {  // uniform
+        __shared__ float s_sum[4];
+        const float inv = row_factor_of_block(ss_row, p.d, p.eps, s_sum);
+        if (threadIdx.x == 0) p.sinv[row] = inv;
     }
 }
 

@@ -18,6 +18,8 @@ struct EmbedParams {
     const float *gain;
     int d;
     RowsRef rr;
+    float *sinv;        // prompt passes: the rows' first RMSNorm factors; null otherwise
+    float eps;
 };
 
 struct AttnParams {
