@@ -990,7 +990,7 @@ bool device_accessible(cllm_ctx *c, const void *p) {
 // MFMA operands, dH = D W through the transposed LM head (K split over workgroups, partials
 // summed in split order), dW = D^T H (if d_weight) and the total (if loss). The workspace grows
 // on demand (hipMalloc); the transposed LM head is built on the first call after the weights
-// are set.
+// are set. The total is formed beside the split sum.
 cllm_status loss_head_enqueue(cllm_ctx *c, const float *T, const float *S, int P, const float *Ar, const int32_t *tg,
                               int A, float omega, float *kl, float *nll, float *dS, float *dA, float *dW,
                               double *loss) {
@@ -1001,14 +1001,16 @@ cllm_status loss_head_enqueue(cllm_ctx *c, const float *T, const float *S, int P
     const int nch = ceil_div(Vp, kLossChunk);
     const int rpad = round_up(Rg, 32);
     const int kstep = c->bf16 ? 32 : 16;  // MFMA k-step (elements)
-    // dH splits: about 512 workgroups over the columns of d and the vocabulary's k-steps
-    const int ks_v = Vp / kstep, n_wg_dh = ceil_div(d, 16 * kLmTiles);
-    const int kc = ceil_div(ks_v, std::max(1, std::min(ks_v, ceil_div(512, n_wg_dh))));
+    // dH splits over the vocabulary's k-steps: one workgroup per CU over the columns of d (bf16, 128
+    // columns each), about 512 smaller ones (fp32)
+    const int ks_v = Vp / kstep, n_wg_dh = ceil_div(d, c->bf16 ? 128 : 16 * kLmTiles);
+    const int want = c->bf16 ? kCUs / n_wg_dh : ceil_div(512, n_wg_dh);
+    const int kc = ceil_div(ks_v, std::max(1, std::min(ks_v, want)));
     const int nsplit = ceil_div(ks_v, kc);
     auto &w = c->loss;
     cllm_status s;
     if ((s = loss_buf(c, &w.A, &w.a, (size_t)cap * d * 4)) || (s = loss_buf(c, &w.Z, &w.z, (size_t)R * Vp)) ||
-        (s = loss_buf(c, &w.D, &w.dd, (size_t)Rg * Vp)) || (s = loss_buf(c, &w.stats, &w.st, (size_t)Rg * nch * 5)) ||
+        (!c->bf16 && (s = loss_buf(c, &w.D, &w.dd, (size_t)Rg * Vp))) || (s = loss_buf(c, &w.stats, &w.st, (size_t)Rg * nch * 5)) ||
         (s = loss_buf(c, &w.Dact, &w.da, (size_t)kMaxRows * Vp * 4)) ||
         (s = loss_buf(c, &w.part_p, &w.part, (size_t)nsplit * Rg * d)))
         return s;
@@ -1034,7 +1036,7 @@ cllm_status loss_head_enqueue(cllm_ctx *c, const float *T, const float *S, int P
     hipEvent_t e0, e1;
     // logits Z = H W^T over the packed LM head (no RMSNorm row factor: the rows are the head's input)
     timing_events(c, CLLM_KT_LOSS_LOGITS, 0, &e0, &e1);
-    HIPCHK(c, launch_pack_rows(c->bf16, T, S, P, Ar, A, d, cap, w.A, st, e0));
+    HIPCHK(c, launch_pack_inputs(c->bf16, T, S, P, Ar, A, d, cap, w.A, rpad, w.HT, st, e0));
     GemmParams g{};
     g.W = c->w_lm;
     g.Ks = c->ks_d;
@@ -1045,19 +1047,25 @@ cllm_status loss_head_enqueue(cllm_ctx *c, const float *T, const float *S, int P
     g.V = V;
     g.Zout = w.Z;
     g.ldz = Vp;
-    // one launch per 64-row tile (each streams the weights once; measured faster than one launch
-    // of two row tiles sharing them), each sized to its rows
-    const int row_tiles = ceil_div(R, kMaxRows);
-    for (int t = 0; t < row_tiles; ++t) {
-        const int rg = rows_to_rg(std::min(kMaxRows, R - t * kMaxRows));
-        g.rt0 = t * kMaxRows / (16 * rg);  // in units of the launch's 16 * rg rows
-        HIPCHK(c, launch_gemm(GEMM_LOGITS, c->bf16, rg, 1, g, st, nullptr, t == row_tiles - 1 ? e1 : nullptr));
+    if (c->bf16) {
+        HIPCHK(c, launch_rows_product(R, g, st, nullptr, e1));
+    } else {
+        // one launch per 64-row tile, each sized to its rows
+        const int row_tiles = ceil_div(R, kMaxRows);
+        for (int t = 0; t < row_tiles; ++t) {
+            const int rg = rows_to_rg(std::min(kMaxRows, R - t * kMaxRows));
+            g.rt0 = t * kMaxRows / (16 * rg);  // in units of the launch's 16 * rg rows
+            HIPCHK(c, launch_gemm(GEMM_LOGITS, false, rg, 1, g, st, nullptr, t == row_tiles - 1 ? e1 : nullptr));
+        }
     }
-    // per-row losses, D, and D (and H) as MFMA operands
+    // per-row losses, D as MFMA operands
     LossParams lp{w.Z, tg, P, A, V, Vp, omega, kl, nll, w.D};
     timing_events(c, CLLM_KT_LOSS_ROWS, 0, &e0, &e1);
-    HIPCHK(c, launch_loss_rows(lp, w.stats, st, e0, nullptr));
-    HIPCHK(c, launch_loss_pack(c->bf16, w.D, Rg, Vp, Vp, kMaxRows, w.Dact, rpad, w.DT, S, P, Ar, d, w.HT, st, e1));
+    HIPCHK(c, launch_loss_stats(lp, w.stats, st, e0));
+    if (c->bf16)
+        HIPCHK(c, launch_loss_grad_pack(lp, w.stats, kMaxRows, reinterpret_cast<uint16_t *>(w.Dact), rpad, w.DT, st, e1));
+    else
+        HIPCHK(c, launch_loss_grad_f32(lp, w.stats, kMaxRows, reinterpret_cast<float *>(w.Dact), st, e1));
     // dH = D W: the streaming GEMM over the transposed LM head, K (the vocabulary) split nsplit ways
     GemmParams h{};
     h.W = w.WT;
@@ -1072,13 +1080,13 @@ cllm_status loss_head_enqueue(cllm_ctx *c, const float *T, const float *S, int P
     h.kc = kc;
     h.zstride = (size_t)Rg * d;
     timing_events(c, CLLM_KT_LOSS_DH, 0, &e0, &e1);
-    HIPCHK(c, launch_gemm(GEMM_LOGITS, c->bf16, rows_to_rg(Rg), 1, h, st, e0, nullptr));
-    HIPCHK(c, launch_loss_dh_sum(w.part_p, nsplit, Rg, d, P, dS, dA, st, e1));
+    HIPCHK(c, c->bf16 ? launch_rows_product(Rg, h, st, e0, nullptr)
+                      : launch_gemm(GEMM_LOGITS, false, rows_to_rg(Rg), 1, h, st, e0, nullptr));
+    HIPCHK(c, launch_loss_dh_sum(w.part_p, nsplit, Rg, d, lp, dS, dA, loss, st, e1));
     if (dW) {
         timing_events(c, CLLM_KT_LOSS_DW, 0, &e0, &e1);
         HIPCHK(c, launch_loss_dw(c->bf16, w.DT, w.HT, Vp, rpad, w.D, Rg, Vp, S, P, Ar, d, V, dW, st, e0, e1));
     }
-    if (loss) HIPCHK(c, launch_loss_total(kl, P, nll, A, omega, loss, st));
     return CLLM_OK;
 }
 

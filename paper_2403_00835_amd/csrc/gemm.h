@@ -88,9 +88,15 @@ hipError_t launch_gemm(GemmKind kind, bool bf16, int rg, int row_tiles, const Ge
 // Prompt (prefill) product of `kind` (QKV, O, gate/up, down) over `rows` rows (bf16 models):
 // workgroup tiles of up to kPromptRows rows with operands shared through LDS; every prompt row
 // takes this path, so its values do not depend on the chunking. O and down run as fixed K ranges
-// (2 and 4) into fp32 partials, then a reduction with the residual epilogue. The row capacity
-// must be a multiple of kPromptRows.
+// (2 and 4) into fp32 partials, then a reduction with the residual epilogue, which also writes the
+// rows' RMSNorm factors to sinv (and the per-16-column sums of squares unless ssq_out is null); QKV
+// and gate/up read them there. The row capacity must be a multiple of kPromptRows.
 hipError_t launch_gemm_prompt(GemmKind kind, int rows, const GemmParams &p, hipStream_t s, hipEvent_t e0,
                               hipEvent_t e1);
+
+// Plain fp32 product of at most 128 rows (bf16): Zout[row][ldz], columns < cols; with kc > 0 grid
+// planes of partial products over K ranges of kc k-steps, zstride floats apart. The row capacity
+// must be a multiple of 64 (of 128 above 64 rows).
+hipError_t launch_rows_product(int rows, const GemmParams &p, hipStream_t s, hipEvent_t e0, hipEvent_t e1);
 
 }  // namespace cllm

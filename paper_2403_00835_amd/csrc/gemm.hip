@@ -437,7 +437,9 @@ __host__ __device__ constexpr int prompt_lds_bytes() {
     return stage > after ? stage : after;
 }
 
-template <int NT, int RG, int WM, int EP, int NB>
+// NA = 2 keeps the even and the odd k-steps' sums apart and adds them at the end: chains half as
+// long, for the loss head's products, whose fp32 results are compared with 64 bits as they are.
+template <int NT, int RG, int WM, int EP, int NB, int NA = 1>
 __global__ __launch_bounds__(kGemmWaves * kWave, 2) void gemm_prompt_kernel(GemmParams p) {
     constexpr Prec P = Prec::BF16;
     constexpr int W = kGemmWaves, WN = W / WM, RGW = RG / WM, NTW = NT / WN;
@@ -526,11 +528,13 @@ __global__ __launch_bounds__(kGemmWaves * kWave, 2) void gemm_prompt_kernel(Gemm
 #pragma unroll
     for (int q = 0; q < NB - 1; ++q) issue(q, q);
 
-    f32x4 acc[RGW][NTW];
+    f32x4 accs[NA][RGW][NTW];
 #pragma unroll
-    for (int r = 0; r < RGW; ++r)
+    for (int q = 0; q < NA; ++q)
 #pragma unroll
-        for (int j = 0; j < NTW; ++j) acc[r][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int r = 0; r < RGW; ++r)
+#pragma unroll
+            for (int j = 0; j < NTW; ++j) accs[q][r][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     u32x4 a[2][2][RGW], b[2][NTW];  // two sets: the k-step being computed, the next one
     auto read_operands = [&](auto set, int buf) {
         constexpr int st = decltype(set)::value;
@@ -555,7 +559,8 @@ __global__ __launch_bounds__(kGemmWaves * kWave, 2) void gemm_prompt_kernel(Gemm
 #pragma unroll
                 for (int r = 0; r < RGW; ++r)
 #pragma unroll
-                    for (int j = 0; j < NTW; ++j) acc[r][j] = mfma_kstep<P>(a[st][pl][r], b[st][j], acc[r][j]);
+                    for (int j = 0; j < NTW; ++j)
+                        accs[st % NA][r][j] = mfma_kstep<P>(a[st][pl][r], b[st][j], accs[st % NA][r][j]);
             // schedule: one LDS read after every few MFMAs
             constexpr int reads = 2 * RGW + NTW, mfmas = 2 * RGW * NTW, per = mfmas >= reads ? mfmas / reads : 1;
 #pragma unroll
@@ -581,6 +586,15 @@ __global__ __launch_bounds__(kGemmWaves * kWave, 2) void gemm_prompt_kernel(Gemm
     if (s < Ks) step(set0, s);
     wait_vm<0>();  // the trailing reloads have landed before the buffers are reused
     __syncthreads();
+    auto &acc = accs[0];
+    if constexpr (NA == 2) {
+#pragma unroll
+        for (int r = 0; r < RGW; ++r)
+#pragma unroll
+            for (int j = 0; j < NTW; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[r][j][e] += accs[NA - 1][r][j][e];
+    }
 
     // The wave's outputs into its LDS block (C layout of a 16 x 16 tile: lane l, register v -> row
     // 4 (l / 16) + v, column l % 16), then out as vectors.
@@ -1342,6 +1356,39 @@ hipError_t launch_gemm_prompt(GemmKind kind, int rows, const GemmParams &p, hipS
     default:
         return hipErrorInvalidValue;
     }
+}
+
+// Plain fp32 product of a few rows (the loss head's logits and dH, bf16): the prompt kernel's
+// tiles over `rows` <= 128 rows, with p.kc > 0 as K ranges into planes of p.Zout.
+template <int NT, int RG, int WM>
+static hipError_t launch_rows_product_t(const GemmParams &p, int rows, int splits, hipStream_t s, hipEvent_t e0,
+                                        hipEvent_t e1) {
+    constexpr int ROWS = 16 * RG, COLS = 16 * NT, NB = 5;
+    constexpr size_t lds = (size_t)prompt_lds_bytes<NT, RG, WM, E_LOGITS, NB>();
+    static_assert(lds <= 160 * 1024, "the LDS of a CU");
+    if (p.rr.cap % ROWS != 0) return hipErrorInvalidValue;
+    GemmParams q = p;
+    q.n_wg = (p.cols + COLS - 1) / COLS;
+    q.row_tiles = (rows + ROWS - 1) / ROWS;
+    const dim3 grid((unsigned)((q.n_wg + 7) / 8 * 8 * q.row_tiles), (unsigned)splits);
+    auto kern = gemm_prompt_kernel<NT, RG, WM, E_LOGITS, NB, 2>;
+    if (e0 || e1)
+        hipExtLaunchKernelGGL(kern, grid, dim3(kGemmWaves * kWave), lds, s, e0, e1, 0, q);
+    else
+        hipLaunchKernelGGL(kern, grid, dim3(kGemmWaves * kWave), lds, s, q);
+    return hipGetLastError();
+}
+
+// Up to 64 rows take 64 x 128 tiles and up to 128 rows 128 x 128 tiles: the head's 32000 columns
+// are then 250 workgroups, one round of the CUs, and the head is streamed once for all rows (two
+// launches of gemm_kernel, one per 64-row tile, took 104 us for 80 rows of the 7B head).
+hipError_t launch_rows_product(int rows, const GemmParams &p, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+    if (rows < 1 || rows > 128 || rows > p.rr.cap || p.lda % 32 != 0 || p.cols % 16 != 0 || p.Ks < 1 || p.kc < 0 ||
+        !p.Zout || p.ldz < p.cols || p.ldz % 4 != 0 || p.zstride % 4 != 0)
+        return hipErrorInvalidValue;
+    const int splits = p.kc > 0 ? (p.Ks + p.kc - 1) / p.kc : 1;
+    if (rows <= 64) return launch_rows_product_t<8, 4, 2>(p, rows, splits, s, e0, e1);
+    return launch_rows_product_t<8, 8, 2>(p, rows, splits, s, e0, e1);
 }
 
 // Grid: column workgroups (ceil(p.cols / (16 * NT))) x row tiles of 16 * RG rows (from row tile

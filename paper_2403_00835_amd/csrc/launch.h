@@ -96,31 +96,33 @@ struct LossParams {
     int P, A, V, ldz;
     float omega;
     float *kl, *nll;   // per pair / per AR row
-    float *D;          // logit gradients [P + A][ldz] (student rows, then AR rows; 0 past V)
+    float *D;          // fp32: logit gradients [P + A][ldz] (student rows, then AR rows; 0 past V)
 };
 // Per-row losses and logit gradients in two passes over vocabulary chunks of kLossChunk entries:
 // per-chunk statistics (stats: [P + A][chunks][5] floats), then their combination in chunk order,
-// the losses and D. e0 (if any) marks the start of the first pass.
+// the losses and the gradients: as operands of the next products (bf16: Dact, the GEMM operand of
+// dH = D W, row capacity cap, K = ldz; DT, that of dW = D^T H with the contraction over rpad rows, two
+// planes of ldz x rpad, zero rows from P + A on), or (fp32) as p.D and Dact. e0 marks the start of
+// the first pass, e1 the end of the last launch.
 constexpr int kLossChunk = 2048;
-hipError_t launch_loss_rows(const LossParams &p, float *stats, hipStream_t s, hipEvent_t e0, hipEvent_t e1);
+hipError_t launch_loss_stats(const LossParams &p, float *stats, hipStream_t s, hipEvent_t e0);
+hipError_t launch_loss_grad_pack(const LossParams &p, const float *stats, int cap, uint16_t *Dact, int rpad, uint16_t *DT,
+                                 hipStream_t s, hipEvent_t e1);
+hipError_t launch_loss_grad_f32(const LossParams &p, const float *stats, int cap, float *Dact, hipStream_t s, hipEvent_t e1);
 // Rows (fp32 [.][d]: np teacher rows T0, np student rows S0, na AR rows R0, in that order) to the
-// two bf16 planes (or one fp32 plane) of a GEMM operand of row capacity cap; e0 marks its start.
-hipError_t launch_pack_rows(bool bf16, const float *T0, const float *S0, int np, const float *R0, int na, int d,
-                            int cap, void *A, hipStream_t s, hipEvent_t e0);
-// D [rows][ldd] as the GEMM operand of dH = D W (Dact: operand order, row capacity cap, K = Vp);
-// in bf16 also D^T and the gradient rows H (S0 rows < np, then R0) as the operands of dW = D^T H
-// with the contraction over rpad rows (DT: 2 planes Vp x rpad; HT: 2 planes d x rpad; zero rows
-// from `rows`). e1 marks the end of the last launch.
-hipError_t launch_loss_pack(bool bf16, const float *D, int rows, int ldd, int Vp, int cap, void *Dact, int rpad,
-                            uint16_t *DT, const float *S0, int np, const float *R0, int d, uint16_t *HT,
-                            hipStream_t s, hipEvent_t e1);
+// two bf16 planes (or one fp32 plane) of a GEMM operand of row capacity cap; in bf16 also the
+// gradient rows (S0, then R0) as HT, the operand of dW = D^T H (two planes of d x rpad, zero rows
+// from np + na on). e0 marks its start.
+hipError_t launch_pack_inputs(bool bf16, const float *T0, const float *S0, int np, const float *R0, int na, int d, int cap,
+                              void *A, int rpad, uint16_t *HT, hipStream_t s, hipEvent_t e0);
 // The packed LM head [Vp][d] repacked as the weight operand of dH = D W (tiles over k-steps of the
 // vocabulary and 16 columns of d); Vp x d elements.
 hipError_t launch_transpose_lm(bool bf16, const uint8_t *W, int Vp, int d, uint8_t *WT, hipStream_t s);
-// dH from the K-split partials [nsplit][rows][d], summed in split order: rows < np to dS [np][d],
-// the others to dA. e1 marks the end.
-hipError_t launch_loss_dh_sum(const float *part, int nsplit, int rows, int d, int np, float *dS, float *dA,
-                              hipStream_t s, hipEvent_t e1);
+// dH from the K-split partials [nsplit][rows][d], summed in split order: rows < p.P to dS [P][d],
+// the others to dA; and, with loss, *loss = sum kl + omega * sum nll, each in row order, in double.
+// e1 marks the end.
+hipError_t launch_loss_dh_sum(const float *part, int nsplit, int rows, int d, const LossParams &p, float *dS, float *dA,
+                              double *loss, hipStream_t s, hipEvent_t e1);
 // dW[v][k] = sum_r D[r][v] H[r][k] for v < V (rows <= 64), H row r = S0 row r for r < np, else
 // R0 row r - np: bf16 from the DT / HT operands, fp32 from D, S0 and R0.
 hipError_t launch_loss_dw(bool bf16, const uint16_t *DT, const uint16_t *HT, int Vp, int rpad, const float *D,
@@ -130,10 +132,6 @@ hipError_t launch_loss_dw(bool bf16, const uint16_t *DT, const uint16_t *HT, int
 // (the mean in a fixed order).
 hipError_t launch_hidden_rows(const float *X, int ldx, int rows, int d, const float *g, float eps, float *out,
                               hipStream_t s);
-// *loss = sum kl[0..np) + omega * sum nll[0..na), each in row order, in double (one thread).
-hipError_t launch_loss_total(const float *kl, int np, const float *nll, int na, float omega, double *loss,
-                             hipStream_t s);
-
 // Seeded synthetic weights, drawn in place: kind 2 fills n floats with 1.0 (norm gains); kinds
 // 0 (float) and 1 (bf16) fill n elements with std x a standard normal deviate: for element i,
 // the Box-Muller pair j = i / 2 of the counter-based draws mix(key ^ 2j), mix(key ^ (2j + 1))

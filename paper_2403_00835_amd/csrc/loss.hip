@@ -112,7 +112,7 @@ __global__ __launch_bounds__(kLossThreads) void loss_stats_kernel(LossParams p, 
     }
 }
 
-// Row statistics, phase 2: the chunks' statistics combined in chunk order (every thread the
+// Row statistics, phase 2 (fp32): the chunks' statistics combined in chunk order (every thread the
 // same), then the row's loss (chunk 0) and its logit gradients over the chunk (0 past V).
 __global__ __launch_bounds__(kLossThreads) void loss_grad_kernel(LossParams p, const float *stats, int nch) {
     const int c = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
@@ -172,71 +172,24 @@ __global__ void pack_rows_kernel(const float *T0, const float *S0, int np, const
     put_act<P>(reinterpret_cast<T *>(A), act_plane(cap, d), act_idx<P>(r, k, d), x);
 }
 
-// Logit gradients D [rows][ldd] (fp32) as MFMA operands, bf16: thread (8 vocabulary entries, 8
-// rows) writes the GEMM operand of dH = D W (rows r < rows, contraction over the vocabulary,
-// Dact: two planes of cap rows x Vp) and the operand of dW = D^T H (contraction over the rows,
-// DT: two planes of Vp x rpad, rows rows..rpad-1 zero).
-__global__ __launch_bounds__(256) void pack_d_kernel(const float *D, int rows, int ldd, int Vp, int cap,
-                                                     uint16_t *Dact, int rpad, uint16_t *DT) {
-    const int nvb = Vp / 8;
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    const int vb = t % nvb, rb = t / nvb;
-    if (rb * 8 >= rpad) return;
-    const int v0 = vb * 8, r0 = rb * 8, ks = rpad / 32;
-    float x[8][8];
+// The same for bf16, eight columns per thread, in one launch with the rows of dW = D^T H (student
+// rows S0, then AR rows R0; zero to rpad) as the operand with contraction over the rows: HT, two
+// planes of d x rpad, thread (column, 8 rows). The first n_rows workgroups pack the GEMM rows.
+__global__ __launch_bounds__(256) void pack_inputs_kernel(const float *T0, const float *S0, int np, const float *R0,
+                                                          int na, int d, int cap, uint16_t *A, int n_rows, int rpad,
+                                                          uint16_t *HT) {
+    if ((int)blockIdx.x < n_rows) {
+        const int i = blockIdx.x * 256 + threadIdx.x, r = i / (d / 8), k = i % (d / 8) * 8;
+        if (r >= 2 * np + na) return;
+        const float *src = r < np ? T0 + (size_t)r * d : r < 2 * np ? S0 + (size_t)(r - np) * d : R0 + (size_t)(r - 2 * np) * d;
+        float x[8];  // the caller's arrays: 4-byte alignment is all that is known
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const int r = r0 + i;
-        f32x4 lo4 = f32x4{0.f, 0.f, 0.f, 0.f}, hi4 = lo4;
-        if (r < rows) {
-            lo4 = *reinterpret_cast<const f32x4 *>(D + (size_t)r * ldd + v0);
-            hi4 = *reinterpret_cast<const f32x4 *>(D + (size_t)r * ldd + v0 + 4);
-        }
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            x[i][e] = lo4[e];
-            x[i][4 + e] = hi4[e];
-        }
+        for (int e = 0; e < 8; ++e) x[e] = src[k + e];
+        put_act8(A, act_plane(cap, d), act_idx<Prec::BF16>(r, k, d), x);
+        return;
     }
-    const size_t pa = act_plane(cap, Vp), pt = (size_t)Vp * rpad;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        if (r0 + i >= rows) break;
-        u32x4 h, l;
-        split8(x[i], h, l);
-        const size_t o = act_idx<Prec::BF16>(r0 + i, v0, Vp);  // 8 consecutive entries: one vector
-        *reinterpret_cast<u32x4 *>(Dact + o) = h;
-        *reinterpret_cast<u32x4 *>(Dact + pa + o) = l;
-    }
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        float y[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) y[i] = x[i][j];
-        u32x4 h, l;
-        split8(y, h, l);
-        const size_t o = tr_idx(v0 + j, r0, ks);
-        *reinterpret_cast<u32x4 *>(DT + o) = h;
-        *reinterpret_cast<u32x4 *>(DT + pt + o) = l;
-    }
-}
-
-// fp32: the GEMM operand of dH = D W only (dW takes D as it is).
-__global__ void pack_d_f32_kernel(const float *D, int rows, int ldd, int Vp, int cap, float *Dact) {
-    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= (size_t)rows * Vp) return;
-    const int r = (int)(i / Vp), v = (int)(i % Vp);
-    Dact[act_idx<Prec::F32>(r, v, Vp)] = D[(size_t)r * ldd + v];
-}
-
-// Rows of dW = D^T H (student rows S0, then AR rows R0; zero from `rows` to rpad) as the bf16
-// operand with contraction over the rows: HT, two planes of d x rpad. Thread: (column, 8 rows).
-__global__ __launch_bounds__(256) void pack_ht_kernel(const float *S0, int np, const float *R0, int rows, int d,
-                                                      int rpad, uint16_t *HT) {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    const int k = t % d, rb = t / d;
-    if (rb * 8 >= rpad) return;
-    const int r0 = rb * 8;
+    const int t = (blockIdx.x - n_rows) * 256 + threadIdx.x, k = t % d, r0 = t / d * 8, rows = np + na;
+    if (r0 >= rpad) return;
     float x[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
@@ -248,6 +201,124 @@ __global__ __launch_bounds__(256) void pack_ht_kernel(const float *S0, int np, c
     const size_t o = tr_idx(k, r0, rpad / 32);
     *reinterpret_cast<u32x4 *>(HT + o) = h;
     *reinterpret_cast<u32x4 *>(HT + (size_t)d * rpad + o) = l;
+}
+
+// Phase 2, bf16: the logit gradients as MFMA operands, without an fp32 copy in memory. Workgroup
+// (512 vocabulary entries, rows 8 y .. 8 y + 7), one wave: the rows' statistics combined in chunk
+// order (staged through LDS), then each thread forms the gradients of 8 vocabulary entries x 8 rows
+// and writes the GEMM operand of dH = D W (rows r < rows, contraction over the vocabulary, Dact: two
+// planes of cap rows x ldz) and the operand of dW = D^T H (contraction over the rows, DT: two planes
+// of ldz x rpad, rows rows .. rpad - 1 zero). Latency bounds it: every logit load is issued before
+// the first is used. At the 7B head
+// (64 rows) 22 us in the place of 10 (fp32 gradients) + 12 (their packing).
+constexpr int kGradThreads = kWave;
+__global__ __launch_bounds__(kGradThreads) void loss_grad_pack_kernel(LossParams p, const float *stats, int nch, int cap,
+                                                                      uint16_t *Dact, int rpad, uint16_t *DT) {
+    struct Row {
+        const float *a, *s;  // teacher and student logits (AR row: a only)
+        float ma, ia, ms, is;
+        int t, kind;         // kind 0: no row, 1: pair, 2: AR row, 3: AR row with a target outside the vocabulary
+    };
+    __shared__ Row s_row[8];
+    extern __shared__ float s_stat[];  // the statistics of the eight rows [8][nch][kStat]
+    const int c = blockIdx.x, r0 = blockIdx.y * 8, tid = threadIdx.x, V = p.V, rows = p.P + p.A;
+    for (int i = tid; i < min(8, rows - r0) * nch * kStat; i += kGradThreads) s_stat[i] = stats[(size_t)r0 * nch * kStat + i];
+    __syncthreads();
+    if (tid < 8) {
+        Row q{p.Z, p.Z, 0.f, 0.f, 0.f, 0.f, 0, 0};  // no row: loads row 0, uses none of it
+        const int b = r0 + tid;
+        const float *st = s_stat + tid * nch * kStat;
+        if (b < p.P) {
+            float ma = -INFINITY, ms = -INFINITY;
+            for (int k = 0; k < nch; ++k) {
+                ma = fmaxf(ma, st[k * kStat + 0]);
+                ms = fmaxf(ms, st[k * kStat + 3]);
+            }
+            float za = 0.f, zs = 0.f, cross = 0.f;
+            for (int k = 0; k < nch; ++k) {
+                const float fa = expf(st[k * kStat + 0] - ma);
+                za += st[k * kStat + 1] * fa;
+                cross += st[k * kStat + 2] * fa;
+                zs += st[k * kStat + 4] * expf(st[k * kStat + 3] - ms);
+            }
+            // KL(p || q) = sum_v p_v (a_v - s_v) - logsumexp(a) + logsumexp(s)
+            if (c == 0) p.kl[b] = cross / za - (ma + logf(za)) + (ms + logf(zs));
+            q = Row{p.Z + (size_t)b * p.ldz, p.Z + (size_t)(p.P + b) * p.ldz, ma, 1.0f / za, ms, 1.0f / zs, 0, 1};
+        } else if (b < rows) {
+            const int i = b - p.P, t = p.targets[i];
+            const float *z = p.Z + (size_t)(2 * p.P + i) * p.ldz;
+            q = Row{z, z, 0.f, 0.f, 0.f, 0.f, t, t < 0 || t >= V ? 3 : 2};
+            if (q.kind == 3) {  // a target outside the vocabulary: NaN loss and gradient row
+                if (c == 0) p.nll[i] = NAN;
+            } else {
+                float mc = -INFINITY;
+                for (int k = 0; k < nch; ++k) mc = fmaxf(mc, st[k * kStat + 0]);
+                float zc = 0.f;
+                for (int k = 0; k < nch; ++k) zc += st[k * kStat + 1] * expf(st[k * kStat + 0] - mc);
+                if (c == 0) p.nll[i] = mc + logf(zc) - z[t];
+                q.ma = mc;
+                q.ia = 1.0f / zc;
+            }
+        }
+        s_row[tid] = q;
+    }
+    __syncthreads();
+    const int v0 = (c * kGradThreads + tid) * 8;
+    if (v0 >= p.ldz) return;  // ldz is a multiple of 64
+    f32x4 za[8][2], zs[8][2];
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            za[i][h] = *reinterpret_cast<const f32x4 *>(s_row[i].a + v0 + 4 * h);
+            zs[i][h] = *reinterpret_cast<const f32x4 *>(s_row[i].s + v0 + 4 * h);
+        }
+    float x[8][8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const Row q = s_row[i];  // uniform
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float a = za[i][e >> 2][e & 3], s = zs[i][e >> 2][e & 3];
+            float y = 0.f;
+            if (q.kind == 1)
+                y = expf(s - q.ms) * q.is - expf(a - q.ma) * q.ia;
+            else if (q.kind == 2)
+                y = p.omega * (expf(a - q.ma) * q.ia - (v0 + e == q.t ? 1.0f : 0.0f));
+            else if (q.kind == 3)
+                y = NAN;
+            x[i][e] = v0 + e < V ? y : 0.f;  // padding columns carry no gradient
+        }
+    }
+    const size_t pa = act_plane(cap, p.ldz), pt = (size_t)p.ldz * rpad;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        if (r0 + i >= rows) break;
+        u32x4 h, l;
+        split8(x[i], h, l);
+        const size_t o = act_idx<Prec::BF16>(r0 + i, v0, p.ldz);  // 8 consecutive entries: one vector
+        *reinterpret_cast<u32x4 *>(Dact + o) = h;
+        *reinterpret_cast<u32x4 *>(Dact + pa + o) = l;
+    }
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        float y[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) y[i] = x[i][j];
+        u32x4 h, l;
+        split8(y, h, l);
+        const size_t o = tr_idx(v0 + j, r0, rpad / 32);
+        *reinterpret_cast<u32x4 *>(DT + o) = h;
+        *reinterpret_cast<u32x4 *>(DT + pt + o) = l;
+    }
+}
+
+// fp32: the GEMM operand of dH = D W only (dW takes D as it is).
+__global__ void pack_d_f32_kernel(const float *D, int rows, int ldd, int Vp, int cap, float *Dact) {
+    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= (size_t)rows * Vp) return;
+    const int r = (int)(i / Vp), v = (int)(i % Vp);
+    Dact[act_idx<Prec::F32>(r, v, Vp)] = D[(size_t)r * ldd + v];
 }
 
 // The packed LM head W [Vp][d] (tiles over (k-step of d, 16 vocabulary rows)) repacked as W^T
@@ -287,16 +358,26 @@ __global__ __launch_bounds__(256) void transpose_lm_kernel(const uint8_t *W, int
     }
 }
 
-// Sum of the K-split partials in split order; rows < np go to dS, the rest to dA.
-__global__ void loss_dh_sum_kernel(const float *part, int nsplit, int n, int np_d, float *dS, float *dA) {
-    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= (size_t)n) return;
-    float s = 0.f;
-    for (int c = 0; c < nsplit; ++c) s += part[(size_t)c * n + i];
-    if (i < (size_t)np_d)
-        dS[i] = s;
-    else
-        dA[i - np_d] = s;
+// Sum of the K-split partials in split order; rows < np go to dS, the rest to dA. The last
+// workgroup forms *loss (if any) = sum kl + omega * sum nll, each sum in row order, in double.
+__global__ __launch_bounds__(256) void loss_dh_sum_kernel(const float *part, int nsplit, int n, int np_d, float *dS, float *dA,
+                                                          const float *kl, int np, const float *nll, int na, float omega,
+                                                          double *loss) {
+    const size_t i = ((size_t)blockIdx.x * 256 + threadIdx.x) * 4;  // rows are a multiple of 64 floats
+    if (i >= (size_t)n) {
+        if (!loss || blockIdx.x != gridDim.x - 1 || threadIdx.x != 255) return;  // the last workgroup holds no rows
+        double ks = 0.0, ns = 0.0;
+        for (int r = 0; r < np; ++r) ks += (double)kl[r];
+        for (int r = 0; r < na; ++r) ns += (double)nll[r];
+        *loss = ks + (double)omega * ns;
+        return;
+    }
+    f32x4 s = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+    for (int c = 0; c < nsplit; ++c) s += *reinterpret_cast<const f32x4 *>(part + (size_t)c * n + i);
+    float *out = i < (size_t)np_d ? dS + i : dA + (i - np_d);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) out[e] = s[e];  // the caller's arrays: 4-byte alignment is all that is known
 }
 
 // One workgroup per row: out = x (.) g / sqrt(mean(x^2) + eps), the LM head's input row.
@@ -311,29 +392,24 @@ __global__ __launch_bounds__(kLossThreads) void hidden_rows_kernel(const float *
     for (int k = threadIdx.x; k < d; k += kLossThreads) out[(size_t)blockIdx.x * d + k] = x[k] * g[k] * inv;
 }
 
-// *loss = sum kl + omega * sum nll, each sum in row order, in double.
-__global__ void loss_total_kernel(const float *kl, int np, const float *nll, int na, float omega, double *loss) {
-    if (threadIdx.x != 0) return;
-    double ks = 0.0, ns = 0.0;
-    for (int i = 0; i < np; ++i) ks += (double)kl[i];
-    for (int i = 0; i < na; ++i) ns += (double)nll[i];
-    *loss = ks + (double)omega * ns;
-}
-
 // dW = D^T H, bf16 operands (hi + lo planes; the products hi hi + hi lo + lo hi, fp32
 // accumulation). Workgroup: 128 vocabulary rows x 128 columns; wave (wv, wk) owns 64 x 64 (4 x 4
-// tiles of 16 x 16); the contraction runs over the rpad rows, 32 per k-step. The wave's block
-// goes out through LDS so that each store instruction writes four whole 256-byte row segments
-// (16 bytes per lane) instead of 64-byte pieces of four rows.
-constexpr int kDwV = 128, kDwK = 128, kDwLd = 64 + 4;  // LDS row stride (floats)
+// tiles of 16 x 16); the contraction runs over the rpad rows, 32 per k-step. Writing dW bounds it
+// (524 MB at the 7B head): the block goes out through LDS in 512-byte row pieces, nontemporal, so
+// that the written lines do not displace the operands and dirty the last-level cache for the next
+// kernels. At the 7B head, 64 rows, random operands, launches back to back: 108 us (4.9 TB/s) against
+// 145 with ordinary stores; 64 x 256 blocks 110; one workgroup per strip of blocks with its H
+// operand kept in registers 104, but slower in a whole call (298 against 286 us); 16-byte stores
+// straight from the registers (64-byte row pieces) 159.
+constexpr int kDwV = 128, kDwK = 128, kDwLd = kDwK + 4;  // LDS row stride (floats)
 __global__ __launch_bounds__(256) void loss_dw_mfma_kernel(const uint16_t *DT, const uint16_t *HT, int Vp, int d,
                                                            int rpad, int V, float *dW) {
-    __shared__ float s_blk[4][64 * kDwLd];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    extern __shared__ float s_blk[];  // kDwV x kDwLd
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, wv = w & 1, wk = w >> 1;
     const int nvt = Vp / 16, nkt = d / 16, ks = rpad / 32;
     // grid x: column blocks (fastest, so consecutive workgroups share the block of D^T through
     // L2), y: vocabulary blocks
-    const int vt0 = blockIdx.y * (kDwV / 16) + (w & 1) * 4, kt0 = blockIdx.x * (kDwK / 16) + (w >> 1) * 4;
+    const int vt0 = blockIdx.y * (kDwV / 16) + wv * 4, kt0 = blockIdx.x * (kDwK / 16) + wk * 4;
     const size_t pd = (size_t)Vp * rpad, ph = (size_t)d * rpad;
     f32x4 acc[4][4];
 #pragma unroll
@@ -365,22 +441,24 @@ __global__ __launch_bounds__(256) void loss_dw_mfma_kernel(const uint16_t *DT, c
                 acc[i][j] = mfma_kstep<Prec::BF16>(al[i], bh[j], acc[i][j]);
             }
     }
-    // C layout: row 4 * (lane / 16) + e of tile (i, j), column lane % 16; into the wave's LDS block
-    float *blk = s_blk[w];
+    // C layout: row 4 * (lane / 16) + e of tile (i, j), column lane % 16
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
         for (int j = 0; j < 4; ++j)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) blk[(16 * i + 4 * (lane >> 4) + e) * kDwLd + 16 * j + (lane & 15)] = acc[i][j][e];
+            for (int e = 0; e < 4; ++e)
+                s_blk[(64 * wv + 16 * i + 4 * (lane >> 4) + e) * kDwLd + 64 * wk + 16 * j + (lane & 15)] = acc[i][j][e];
     __syncthreads();
-    // rows of the block: 16 lanes per row (16 bytes each), four rows per store
-    const int k = 16 * kt0 + 4 * (lane & 15);
+    // two rows of the block per store: 32 lanes of 16 bytes each
+    const int c = 4 * (lane & 31), k = blockIdx.x * kDwK + c;
     if (k < d) {
 #pragma unroll 4
-        for (int r = lane >> 4; r < 64; r += 4) {
-            const int v = 16 * vt0 + r;
-            if (v < V) *reinterpret_cast<f32x4 *>(dW + (size_t)v * d + k) = *reinterpret_cast<const f32x4 *>(blk + r * kDwLd + 4 * (lane & 15));
+        for (int r = 2 * w + (lane >> 5); r < kDwV; r += 8) {
+            const int v = kDwV * blockIdx.y + r;
+            if (v < V)
+                __builtin_nontemporal_store(*reinterpret_cast<const f32x4 *>(s_blk + r * kDwLd + c),
+                                            reinterpret_cast<f32x4 *>(dW + (size_t)v * d + k));
         }
     }
 }
@@ -414,50 +492,52 @@ __global__ __launch_bounds__(256) void loss_dw_f32_kernel(const float *D, int ro
         }
 }
 
-hipError_t launch_loss_rows(const LossParams &p, float *stats, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-    if (p.P < 0 || p.A < 0 || p.P + p.A < 1 || p.V < 1 || p.ldz < p.V) return hipErrorInvalidValue;
+static bool loss_params_ok(const LossParams &p) { return p.P >= 0 && p.A >= 0 && p.P + p.A >= 1 && p.V >= 1 && p.ldz >= p.V; }
+
+hipError_t launch_loss_stats(const LossParams &p, float *stats, hipStream_t s, hipEvent_t e0) {
+    if (!loss_params_ok(p)) return hipErrorInvalidValue;
     const int nch = (p.ldz + kLossChunk - 1) / kLossChunk;  // = chunks of V (ldz - V < 64 <= kLossChunk)
-    const dim3 grid(nch, p.P + p.A);
-    if (e0)
-        hipExtLaunchKernelGGL(loss_stats_kernel, grid, dim3(kLossThreads), 0, s, e0, nullptr, 0, p, stats, nch);
-    else
-        hipLaunchKernelGGL(loss_stats_kernel, grid, dim3(kLossThreads), 0, s, p, stats, nch);
-    if (e1)
-        hipExtLaunchKernelGGL(loss_grad_kernel, grid, dim3(kLossThreads), 0, s, nullptr, e1, 0, p,
-                              (const float *)stats, nch);
-    else
-        hipLaunchKernelGGL(loss_grad_kernel, grid, dim3(kLossThreads), 0, s, p, (const float *)stats, nch);
+    hipExtLaunchKernelGGL(loss_stats_kernel, dim3(nch, p.P + p.A), dim3(kLossThreads), 0, s, e0, nullptr, 0, p, stats, nch);
     return hipGetLastError();
 }
 
-hipError_t launch_pack_rows(bool bf16, const float *T0, const float *S0, int np, const float *R0, int na, int d,
-                            int cap, void *A, hipStream_t s, hipEvent_t e0) {
+hipError_t launch_loss_grad_f32(const LossParams &p, const float *stats, int cap, float *Dact, hipStream_t s, hipEvent_t e1) {
+    const int rows = p.P + p.A;
+    if (!loss_params_ok(p) || rows > cap) return hipErrorInvalidValue;
+    const int nch = (p.ldz + kLossChunk - 1) / kLossChunk;
+    hipLaunchKernelGGL(loss_grad_kernel, dim3(nch, rows), dim3(kLossThreads), 0, s, p, stats, nch);
+    const size_t n = (size_t)rows * p.ldz;
+    hipExtLaunchKernelGGL(pack_d_f32_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, nullptr, e1, 0,
+                          (const float *)p.D, rows, p.ldz, p.ldz, cap, Dact);
+    return hipGetLastError();
+}
+
+hipError_t launch_loss_grad_pack(const LossParams &p, const float *stats, int cap, uint16_t *Dact, int rpad, uint16_t *DT,
+                                 hipStream_t s, hipEvent_t e1) {
+    const int rows = p.P + p.A;
+    if (!loss_params_ok(p) || rows > cap || p.ldz % 64 != 0 || rpad % 32 != 0 || rpad < rows) return hipErrorInvalidValue;
+    const int nch = (p.ldz + kLossChunk - 1) / kLossChunk;
+    const size_t lds = (size_t)8 * nch * kStat * sizeof(float);
+    if (lds > 96 * 1024) return hipErrorInvalidValue;  // a vocabulary of more than a million entries
+    hipExtLaunchKernelGGL(loss_grad_pack_kernel, dim3((p.ldz / 8 + kGradThreads - 1) / kGradThreads, rpad / 8), dim3(kGradThreads), lds, s, nullptr, e1, 0, p, stats,
+                          nch, cap, Dact, rpad, DT);
+    return hipGetLastError();
+}
+
+hipError_t launch_pack_inputs(bool bf16, const float *T0, const float *S0, int np, const float *R0, int na, int d, int cap,
+                              void *A, int rpad, uint16_t *HT, hipStream_t s, hipEvent_t e0) {
     const int rows = 2 * np + na;
-    if (np < 0 || na < 0 || rows < 1 || rows > cap || d % 32 != 0) return hipErrorInvalidValue;
-    const size_t n = (size_t)rows * d;
-    const dim3 grid((unsigned)((n + 255) / 256));
-    auto kern = bf16 ? pack_rows_kernel<Prec::BF16> : pack_rows_kernel<Prec::F32>;
-    hipExtLaunchKernelGGL(kern, grid, dim3(256), 0, s, e0, nullptr, 0, T0, S0, np, R0, na, d, cap, A);
-    return hipGetLastError();
-}
-
-hipError_t launch_loss_pack(bool bf16, const float *D, int rows, int ldd, int Vp, int cap, void *Dact, int rpad,
-                            uint16_t *DT, const float *S0, int np, const float *R0, int d, uint16_t *HT,
-                            hipStream_t s, hipEvent_t e1) {
-    if (rows < 1 || rows > cap || ldd < Vp || Vp % 64 != 0 || d % 64 != 0) return hipErrorInvalidValue;
+    if (np < 0 || na < 0 || rows < 1 || rows > cap || d % 64 != 0) return hipErrorInvalidValue;
     if (!bf16) {
-        const size_t n = (size_t)rows * Vp;
-        hipExtLaunchKernelGGL(pack_d_f32_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, nullptr, e1, 0,
-                              D, rows, ldd, Vp, cap, reinterpret_cast<float *>(Dact));
+        const size_t n = (size_t)rows * d;
+        hipExtLaunchKernelGGL(pack_rows_kernel<Prec::F32>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, e0, nullptr,
+                              0, T0, S0, np, R0, na, d, cap, A);
         return hipGetLastError();
     }
-    if (rpad % 32 != 0 || rpad < rows || rpad > cap || np < 0 || np > rows) return hipErrorInvalidValue;
-    const size_t nd = (size_t)(Vp / 8) * (rpad / 8);
-    hipLaunchKernelGGL(pack_d_kernel, dim3((unsigned)((nd + 255) / 256)), dim3(256), 0, s, D, rows, ldd, Vp, cap,
-                       reinterpret_cast<uint16_t *>(Dact), rpad, DT);
-    const size_t nh = (size_t)d * (rpad / 8);
-    hipExtLaunchKernelGGL(pack_ht_kernel, dim3((unsigned)((nh + 255) / 256)), dim3(256), 0, s, nullptr, e1, 0, S0, np,
-                          R0, rows, d, rpad, HT);
+    if (rpad % 32 != 0 || rpad < np + na) return hipErrorInvalidValue;
+    const int n_rows = (rows * (d / 8) + 255) / 256, n_ht = (d * (rpad / 8) + 255) / 256;
+    hipExtLaunchKernelGGL(pack_inputs_kernel, dim3(n_rows + n_ht), dim3(256), 0, s, e0, nullptr, 0, T0, S0, np, R0, na, d,
+                          cap, reinterpret_cast<uint16_t *>(A), n_rows, rpad, HT);
     return hipGetLastError();
 }
 
@@ -473,12 +553,12 @@ hipError_t launch_transpose_lm(bool bf16, const uint8_t *W, int Vp, int d, uint8
     return hipGetLastError();
 }
 
-hipError_t launch_loss_dh_sum(const float *part, int nsplit, int rows, int d, int np, float *dS, float *dA,
-                              hipStream_t s, hipEvent_t e1) {
-    if (nsplit < 1 || rows < 1 || np < 0 || np > rows) return hipErrorInvalidValue;
+hipError_t launch_loss_dh_sum(const float *part, int nsplit, int rows, int d, const LossParams &p, float *dS, float *dA,
+                              double *loss, hipStream_t s, hipEvent_t e1) {
+    if (nsplit < 1 || rows < 1 || p.P < 0 || p.P > rows || d % 64 != 0) return hipErrorInvalidValue;
     const int n = rows * d;
-    hipExtLaunchKernelGGL(loss_dh_sum_kernel, dim3((n + 255) / 256), dim3(256), 0, s, nullptr, e1, 0, part, nsplit, n,
-                          np * d, dS, dA);
+    hipExtLaunchKernelGGL(loss_dh_sum_kernel, dim3((n / 4 + 255) / 256 + 1), dim3(256), 0, s, nullptr, e1, 0, part, nsplit, n,
+                          p.P * d, dS, dA, (const float *)p.kl, p.P, (const float *)p.nll, p.A, p.omega, loss);
     return hipGetLastError();
 }
 
@@ -486,12 +566,6 @@ hipError_t launch_hidden_rows(const float *X, int ldx, int rows, int d, const fl
                               hipStream_t s) {
     if (rows < 1 || d < 1 || ldx < d) return hipErrorInvalidValue;
     hipLaunchKernelGGL(hidden_rows_kernel, dim3(rows), dim3(kLossThreads), 0, s, X, ldx, d, g, eps, out);
-    return hipGetLastError();
-}
-
-hipError_t launch_loss_total(const float *kl, int np, const float *nll, int na, float omega, double *loss,
-                             hipStream_t s) {
-    hipLaunchKernelGGL(loss_total_kernel, dim3(1), dim3(64), 0, s, kl, np, nll, na, omega, loss);
     return hipGetLastError();
 }
 
@@ -503,10 +577,11 @@ hipError_t launch_loss_dw(bool bf16, const uint16_t *DT, const uint16_t *HT, int
     if (bf16) {
         if (rpad % 32 != 0 || rpad < rows) return hipErrorInvalidValue;
         const dim3 grid((d + kDwK - 1) / kDwK, (Vp + kDwV - 1) / kDwV);
+        const size_t lds = (size_t)kDwV * kDwLd * sizeof(float);
         if (e0)
-            hipExtLaunchKernelGGL(loss_dw_mfma_kernel, grid, dim3(256), 0, s, e0, e1, 0, DT, HT, Vp, d, rpad, V, dW);
+            hipExtLaunchKernelGGL(loss_dw_mfma_kernel, grid, dim3(256), lds, s, e0, e1, 0, DT, HT, Vp, d, rpad, V, dW);
         else
-            hipLaunchKernelGGL(loss_dw_mfma_kernel, grid, dim3(256), 0, s, DT, HT, Vp, d, rpad, V, dW);
+            hipLaunchKernelGGL(loss_dw_mfma_kernel, grid, dim3(256), lds, s, DT, HT, Vp, d, rpad, V, dW);
         return hipGetLastError();
     }
     const dim3 grid((V + 63) / 64, d / 64);
