@@ -123,8 +123,8 @@ __device__ __forceinline__ void put_act8(uint16_t *base, size_t plane, size_t i,
 }
 
 // The RMSNorm factor 1/sqrt(sum / K + eps) of one row from its workgroup's partial sums of squares
-// (at most four waves): a fixed tree over each wave's lanes, then the waves in order. s_sum: LDS.
-__device__ __forceinline__ float row_factor_of_block(float sum, int K, float eps, float (&s_sum)[4]) {
+// (at most eight waves): a fixed tree over each wave's lanes, then the waves in order. s_sum: LDS.
+__device__ __forceinline__ float row_factor_of_block(float sum, int K, float eps, float (&s_sum)[8]) {
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) sum += __shfl_xor(sum, off);
     if ((threadIdx.x & 63) == 0) s_sum[threadIdx.x >> 6] = sum;

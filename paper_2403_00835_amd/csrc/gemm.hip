@@ -1212,12 +1212,12 @@ static hipError_t launch_split_t(const GemmParams &p, int row_tiles, hipStream_t
 // sums are added in a fixed tree (lanes, then waves in order), so the factor depends on the row
 // and the model's width only.
 template <int NS>
-__global__ __launch_bounds__(256) void prompt_reduce_kernel(GemmParams p, size_t zstride) {
+__global__ __launch_bounds__(512) void prompt_reduce_kernel(GemmParams p, size_t zstride) {
     constexpr Prec P = Prec::BF16;
     const int row = blockIdx.x, tid = threadIdx.x;
     request_together(p.rr.tab, p.part, p.Xout, p.gain, p.An, p.ldx, p.cols, p.rr.cap);
     if (row >= p.rr.tab->R) return;
-    __shared__ float s_sum[4];
+    __shared__ float s_sum[8];
     float ss_row = 0.0f;
     for (int g = tid; g < p.cols / 8; g += blockDim.x) {
         const int c0 = 8 * g;
@@ -1259,8 +1259,9 @@ __global__ __launch_bounds__(256) void prompt_reduce_kernel(GemmParams p, size_t
 static hipError_t launch_prompt_reduce(const GemmParams &p, int nsplit, size_t zstride, int rows, hipStream_t s,
                                        hipEvent_t e1) {
     if (!p.sinv || !p.gain || p.cols % 16 != 0) return hipErrorInvalidValue;
-    // whole waves, at most 256 threads: one 8-column vector each where the width allows it
-    const int threads = std::min(256, (p.cols / 8 + kWave - 1) / kWave * kWave);
+    // whole waves, at most 512 threads: one 8-column vector each up to 4096 columns (with 256
+    // threads, two vectors each, the 512-row down reduction took 18 us)
+    const int threads = std::min(512, (p.cols / 8 + kWave - 1) / kWave * kWave);
     auto kern = nsplit == 1 ? prompt_reduce_kernel<1> : nsplit == 2 ? prompt_reduce_kernel<2>
                 : nsplit == 3 ? prompt_reduce_kernel<3> : prompt_reduce_kernel<4>;
     if (e1)

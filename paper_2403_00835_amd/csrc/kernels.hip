@@ -75,7 +75,7 @@ __global__ __launch_bounds__(256) void embed_kernel(EmbedParams p) {
         ss_row += sum;
     }
     if (p.sinv) {  // uniform
-        __shared__ float s_sum[4];
+        __shared__ float s_sum[8];
         const float inv = row_factor_of_block(ss_row, p.d, p.eps, s_sum);
         if (threadIdx.x == 0) p.sinv[row] = inv;
     }
@@ -463,6 +463,203 @@ __global__ __launch_bounds__(kWave * RG) void attn_partial_kernel(AttnParams p) 
     }
 }
 
+// ------------------------------------------------------------------------------------------
+// Attention of prompt rows (prefill passes, bf16, head_dim <= 128): one kernel, no partials in
+// memory. Workgroup (head h, 64 rows of a batch entry), 8 waves: 4 row groups of 16 rows x the even
+// and the odd 64-key chunks (at absolute positions). A wave walks its chunks with a running maximum
+// per row (rescaling its sum and output when the maximum grows); the two halves are merged through
+// LDS at the end. Per chunk the arithmetic is attn_partial_kernel's: S^T = K Q^T (query hi and lo
+// planes), base-2 softmax in fp32, O^T += V^T P^T (probabilities hi and lo). The chunks of a
+// pair of steps come into LDS by DMA, once for all waves, one pair ahead. A row's value depends on
+// its position and the cache only, not on the rows or the pass it is computed with.
+//
+// What bounds it: LDS reads (each row group reads the whole chunk) and the softmax's VALU work,
+// about as long as the MFMAs. Against the chunk-parallel pair, which wrote and read the partials
+// (rows x head_dim x 4 B per chunk, as much as the K and V they summarise), 512 rows, 32 heads of
+// 128: 39 -> 19 us at 512 keys, 92 -> 37 us on average over the four passes of 1999 keys.
+// ------------------------------------------------------------------------------------------
+constexpr int kPromptAttnRows = 64;
+
+template <int HD>
+__host__ __device__ constexpr int prompt_attn_lds_bytes() {
+    constexpr int stage = 2 * 2 * kAttnChunk * HD * 2 * 2;              // [2 buffers][2 chunks][K, V]
+    constexpr int merge = 4 * kWave * (HD / 4 + 2) * (int)sizeof(float);  // one half's state per row group
+    return stage > merge ? stage : merge;
+}
+
+template <int HD>
+__global__ __launch_bounds__(8 * kWave, 2) void attn_prompt_kernel(AttnParams p) {
+    constexpr Prec P = Prec::BF16;
+    using PT = PrecT<P>;
+    constexpr int NKK = HD / PT::KSTEP, NDT = HD / 16;
+    constexpr int NKB = 4 * NKK, NVB = 2 * NDT, BLK = NKB + NVB;  // 1 KiB blocks of a chunk
+    constexpr int NLW = 2 * BLK / 8;                              // DMA loads per wave and pair of chunks
+    const RowTab *tab = p.rr.tab;
+    request_together(tab, p.Q, p.Kc, p.Vt, p.kv_seq, p.ctx_alloc, p.rr.cap, p.d, p.O);
+    const int h = blockIdx.x, b = blockIdx.z;
+    const int rbase = (int)(gridDim.y - 1 - blockIdx.y) * kPromptAttnRows;  // the longest rows first
+    const int nseq = tab->nseq, m = tab->m[b], L = tab->L[b], r0 = tab->r0[b], slot = tab->seq[b];
+    request_together(nseq, m, L, r0, slot);
+    if (b >= nseq || rbase >= m) return;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int rg = w & 3, half = w >> 2;
+    const int g = lane >> 4, r16 = lane & 15;
+    const int d = p.d;
+    const int qi = rbase + 16 * rg + r16;     // row within the entry
+    const int qld = min(r0 + qi, p.rr.cap - 1);  // rows past the entry load in-bounds filler
+    const int qpos = L + qi;
+    const int npair = ((L + min(m - 1, rbase + kPromptAttnRows - 1)) / kAttnChunk + 2) / 2;  // pairs of chunks with a visible key
+    const int wlast = L + min(m - 1, rbase + 16 * rg + 15);  // the wave's last position
+    const bool live = rbase + 16 * rg < m;                   // uniform over the wave
+    const size_t kvo = (size_t)slot * p.kv_seq + (size_t)h * p.ctx_alloc * HD;
+    const uint16_t *Kh = reinterpret_cast<const uint16_t *>(p.Kc) + kvo;
+    const uint16_t *Vh = reinterpret_cast<const uint16_t *>(p.Vt) + kvo;
+    const uint16_t *Q = reinterpret_cast<const uint16_t *>(p.Q);
+
+    extern __shared__ u32x4 s_kv[];  // [2 buffers][2 chunks][BLK][64]
+    // A chunk's K blocks (and its V blocks) are contiguous in the cache: block i of chunk c at
+    // (c BLKS + i) KiB. The cache holds whole chunks, so the second chunk of the last pair (clamped
+    // to the last one) is in bounds.
+    const int last_chunk = p.ctx_alloc / kAttnChunk - 1;
+    auto issue = [&](int pair, int buf) {
+#pragma unroll
+        for (int i = 0; i < NLW; ++i) {
+            const int t = w + 8 * i, ch = t / BLK, blk = t % BLK;
+            const int c = min(2 * pair + ch, last_chunk);
+            const uint16_t *src = blk < NKB ? Kh + ((size_t)c * NKB + blk) * (kWave * 8)
+                                            : Vh + ((size_t)c * NVB + blk - NKB) * (kWave * 8);
+            __builtin_amdgcn_global_load_lds(static_cast<const void *>(src + lane * 8),
+                                             (__attribute__((address_space(3))) void *)(s_kv + (size_t)(buf * 2 * BLK + t) * kWave),
+                                             16, 0, 0);
+        }
+    };
+    u32x4 qv[2][NKK];
+#pragma unroll
+    for (int kk = 0; kk < NKK; ++kk)
+#pragma unroll
+        for (int pl = 0; pl < 2; ++pl)
+            qv[pl][kk] = *reinterpret_cast<const u32x4 *>(
+                Q + pl * act_plane(p.rr.cap, d) + act_idx<P>(qld, h * HD + kk * PT::KSTEP + g * PT::VEC, d));
+    issue(0, 0);
+
+    float M = -INFINITY, l = 0.0f;
+    f32x4 o[NDT];
+#pragma unroll
+    for (int dt = 0; dt < NDT; ++dt) o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int it = 0; it < npair; ++it) {
+        wait_vm_lds<0>();    // this wave's blocks of the pair have landed, its reads of the other buffer are done
+        barrier_no_fence();  // every wave's
+        if (it + 1 < npair) issue(it + 1, (it + 1) & 1);
+        const int key0 = (2 * it + half) * kAttnChunk;
+        if (!live || key0 > wlast) continue;  // no row of the wave sees the chunk
+        const u32x4 *kv = s_kv + (size_t)((it & 1) * 2 + half) * BLK * kWave + lane;
+        f32x4 st[4];
+#pragma unroll
+        for (int kt = 0; kt < 4; ++kt) {
+            st[kt] = f32x4{0.f, 0.f, 0.f, 0.f};
+            u32x4 kb[NKK];
+#pragma unroll
+            for (int kk = 0; kk < NKK; ++kk) kb[kk] = kv[(kt * NKK + kk) * kWave];
+#pragma unroll
+            for (int pl = 0; pl < 2; ++pl)
+#pragma unroll
+                for (int kk = 0; kk < NKK; ++kk) st[kt] = mfma_kstep<P>(kb[kk], qv[pl][kk], st[kt]);
+        }
+        // st[kt][v] = S^T[key0 + 16kt + 4g + v][row r16]
+        float mx = -INFINITY;
+#pragma unroll
+        for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int key = key0 + 16 * kt + 4 * g + v;
+                const float sc = key <= qpos ? st[kt][v] * p.scale_log2 : -INFINITY;
+                st[kt][v] = sc;
+                mx = fmaxf(mx, sc);
+            }
+        mx = fmaxf(mx, __shfl_xor(mx, 16));
+        mx = fmaxf(mx, __shfl_xor(mx, 32));
+        const float Mn = fmaxf(M, mx);
+        if (__any(Mn > M)) {  // some row's maximum grew: rescale (by exactly 1 where it did not)
+            const float sc = M == -INFINITY ? 0.0f : exp2f(M - Mn);
+            l *= sc;
+#pragma unroll
+            for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) o[dt][v] *= sc;
+            M = Mn;
+        }
+        float ls = 0.0f;
+#pragma unroll
+        for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const float pr = (M == -INFINITY || st[kt][v] == -INFINITY) ? 0.0f : exp2f(st[kt][v] - M);
+                st[kt][v] = pr;
+                ls += pr;
+            }
+        l += ls;  // this lane's keys; the lanes of a row are added at the end
+        u32x4 ph[2], plo[2];
+#pragma unroll
+        for (int kp = 0; kp < 2; ++kp) {
+            // P = hi + lo, hi = bf16(P), lo = bf16(P - hi): the probabilities keep ~2^-17
+            const f32x4 pa = st[2 * kp], pb = st[2 * kp + 1];
+            const float pv[8] = {pa[0], pa[1], pa[2], pa[3], pb[0], pb[1], pb[2], pb[3]};
+            uint32_t hi[8], lo[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                hi[q] = f2bf(pv[q]);
+                lo[q] = f2bf(pv[q] - bf2f((uint16_t)hi[q]));
+            }
+            ph[kp] = u32x4{hi[0] | (hi[1] << 16), hi[2] | (hi[3] << 16), hi[4] | (hi[5] << 16), hi[6] | (hi[7] << 16)};
+            plo[kp] = u32x4{lo[0] | (lo[1] << 16), lo[2] | (lo[3] << 16), lo[4] | (lo[5] << 16), lo[6] | (lo[7] << 16)};
+        }
+#pragma unroll
+        for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+            for (int kp = 0; kp < 2; ++kp) {
+                const u32x4 vb = kv[(NKB + kp * NDT + dt) * kWave];
+                o[dt] = mfma_kstep<P>(vb, ph[kp], o[dt]);
+                o[dt] = mfma_kstep<P>(vb, plo[kp], o[dt]);
+            }
+    }
+    l += __shfl_xor(l, 16);
+    l += __shfl_xor(l, 32);
+    // merge: the odd half's state through LDS, lane by lane (the same row and dims)
+    wait_vm_lds<0>();
+    __syncthreads();
+    float *s_m = reinterpret_cast<float *>(s_kv) + (size_t)rg * (HD / 4 + 2) * kWave + lane;
+    if (half == 1) {
+#pragma unroll
+        for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) s_m[(4 * dt + v) * kWave] = o[dt][v];
+        s_m[(HD / 4) * kWave] = M;
+        s_m[(HD / 4 + 1) * kWave] = l;
+    }
+    __syncthreads();
+    if (half == 1 || qi >= m) return;
+    const float M1 = s_m[(HD / 4) * kWave], l1 = s_m[(HD / 4 + 1) * kWave];
+    const float Mt = fmaxf(M, M1);  // chunk 0 holds a visible key of every row: finite
+    const float w0 = M == -INFINITY ? 0.0f : exp2f(M - Mt), w1 = M1 == -INFINITY ? 0.0f : exp2f(M1 - Mt);
+    const float den = w0 * l + w1 * l1;
+    uint16_t *O = reinterpret_cast<uint16_t *>(p.O);
+    const size_t plane = act_plane(p.rr.cap, d);
+#pragma unroll
+    for (int dt = 0; dt < NDT; ++dt) {
+        alignas(8) uint16_t hi[4], lo[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const float x = (w0 * o[dt][v] + w1 * s_m[(4 * dt + v) * kWave]) / den;
+            hi[v] = f2bf(x);
+            lo[v] = f2bf(x - bf2f(hi[v]));
+        }
+        const size_t i = act_idx<P>(r0 + qi, h * HD + 16 * dt + 4 * g, d);  // four consecutive dims of a vector
+        *reinterpret_cast<u32x2 *>(O + i) = *reinterpret_cast<const u32x2 *>(hi);
+        *reinterpret_cast<u32x2 *>(O + plane + i) = *reinterpret_cast<const u32x2 *>(lo);
+    }
+}
+
 // Combine the chunk partials of one (head, row) in chunk order and write the O operand.
 // Wave 0 derives the chunk weights w_c = 2^(m_c - M) into LDS; every thread (one output dim)
 // then sums w_c * O_c in chunk order, and the denominator sum w_c * l_c in chunk order beside
@@ -842,6 +1039,24 @@ hipError_t launch_embed(bool bf16, int rows, const EmbedParams &p, hipStream_t s
     else
         hipLaunchKernelGGL(kern, dim3(rows), dim3(256), 0, s, p);
     return hipGetLastError();
+}
+
+hipError_t launch_attn_prompt(int max_rows, int nseq, const AttnParams &p, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+    if (max_rows < 1 || nseq < 1 || nseq > kMaxSeqs || p.ctx_alloc % kAttnChunk != 0) return hipErrorInvalidValue;
+    const dim3 grid(p.n_heads, (max_rows + kPromptAttnRows - 1) / kPromptAttnRows, nseq), block(8 * kWave);
+    auto launch = [&](auto kern, int lds) {
+        if (e0)
+            hipExtLaunchKernelGGL(kern, grid, block, lds, s, e0, e1, 0, p);
+        else
+            hipLaunchKernelGGL(kern, grid, block, lds, s, p);
+        return hipGetLastError();
+    };
+    switch (p.hd) {
+    case 32: return launch(attn_prompt_kernel<32>, prompt_attn_lds_bytes<32>());
+    case 64: return launch(attn_prompt_kernel<64>, prompt_attn_lds_bytes<64>());
+    case 128: return launch(attn_prompt_kernel<128>, prompt_attn_lds_bytes<128>());
+    default: return hipErrorInvalidValue;
+    }
 }
 
 template <Prec P, int HD>
