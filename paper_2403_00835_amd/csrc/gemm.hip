@@ -1512,6 +1512,22 @@ static hipError_t launch_down(const GemmParams &p, int row_tiles, hipStream_t s,
     return hipGetLastError();
 }
 
+// Small models: a launch whose K is at most kShortKs k-steps (eight per wave) is a latency chain, not
+// a stream. It takes the smallest column tile whose workgroups fit the CUs in one round (more CUs
+// pull, and a workgroup's tree and epilogue are shorter) with up to four k-steps of a wave in flight,
+// which at K = 768 is all of them. The k-steps of a wave and the tree are the same for every tile
+// and depth, so the values are those of the larger tiles. Measured at d 768, FFN 2048 (one row,
+// us a launch): QKV 6.0 -> 5.0 (tiles of 48 -> 16 columns: 48 -> 144 workgroups), gate/up 7.0 ->
+// 5.2 (96 -> 32: 43 -> 128), down with its reduction 6.2 and a launch gap -> 5.2. Above 64 k-steps
+// the larger tiles and the K ranges stay: the launch is a stream there (d 4096: QKV 256 workgroups
+// with the larger tile already, down 21.5 us in one launch against 19.1 with its reduction).
+constexpr int kShortKs = 64, kShortDepth = 4;
+
+// The down product of such a K is one launch, without K ranges and their reduction. The rule reads
+// the model's shape only: every row count takes the same order.
+static bool short_k(const GemmParams &p) { return p.Ks <= kShortKs; }
+static bool one_round(const GemmParams &p, int nt) { return ((p.cols >> 4) + nt - 1) / nt <= kCUs; }
+
 template <Prec P, int RG>
 static hipError_t launch_gemm_rg(GemmKind kind, const GemmParams &p, int row_tiles, hipStream_t s, hipEvent_t e0,
                                  hipEvent_t e1) {
@@ -1531,7 +1547,7 @@ static hipError_t launch_gemm_rg(GemmKind kind, const GemmParams &p, int row_til
         // same values); at 7B, 96 / 160 / 256 / 512 rows: gate/up 59 / 112 / 115 / 221 us against
         // 77 / 110 / 144 / 278, down (with its reduction) 36 / 62 / 62 / 116 against 46 / 62 / 80 / 143
         if (kind == GEMM_GATE_UP) return launch_rows_t<kRowsNtGateUp, E_SWIGLU, kRowsNbGateUp, 6, 2>(p, row_tiles, s, e0, e1);
-        if (kind == GEMM_DOWN) return launch_down<P, RG, 3, true>(p, row_tiles, s, e0, e1);
+        if (kind == GEMM_DOWN && !short_k(p)) return launch_down<P, RG, 3, true>(p, row_tiles, s, e0, e1);
     }
     if (row_tiles > 1) {
         // More than 64 rows (measured at 160 and 512 rows, 7B): QKV and gate/up take 96-column
@@ -1544,6 +1560,7 @@ static hipError_t launch_gemm_rg(GemmKind kind, const GemmParams &p, int row_til
         case GEMM_O:
             return launch_gemm_t<P, 4, RG, E_RESID, 3>(p, row_tiles, s, e0, e1);
         case GEMM_DOWN:
+            if (short_k(p)) return launch_gemm_t<P, 4, RG, E_RESID, 3>(p, row_tiles, s, e0, e1);
             return launch_down<P, RG, 3>(p, row_tiles, s, e0, e1);
         case GEMM_GATE_UP:
             return launch_gemm_t<P, 6, RG, E_SWIGLU, 2>(p, row_tiles, s, e0, e1);
@@ -1556,12 +1573,16 @@ static hipError_t launch_gemm_rg(GemmKind kind, const GemmParams &p, int row_til
     }
     switch (kind) {
     case GEMM_QKV:
+        if (short_k(p) && one_round(p, 1)) return launch_gemm_t<P, 1, RG, E_QKV, kShortDepth>(p, row_tiles, s, e0, e1);
         return launch_gemm_t<P, kNtQkv, RG, E_QKV>(p, row_tiles, s, e0, e1);
     case GEMM_O:
+        if (short_k(p)) return launch_gemm_t<P, kNtResid, RG, E_RESID, kShortDepth>(p, row_tiles, s, e0, e1);
         return launch_gemm_t<P, kNtResid, RG, E_RESID>(p, row_tiles, s, e0, e1);
     case GEMM_DOWN:
+        if (short_k(p)) return launch_gemm_t<P, kNtResid, RG, E_RESID, kShortDepth>(p, row_tiles, s, e0, e1);
         return launch_down<P, RG, kGemmDepth>(p, row_tiles, s, e0, e1);
     case GEMM_GATE_UP:
+        if (short_k(p) && one_round(p, 2)) return launch_gemm_t<P, 2, RG, E_SWIGLU, kShortDepth>(p, row_tiles, s, e0, e1);
         return launch_gemm_t<P, kNtGateUp, RG, E_SWIGLU>(p, row_tiles, s, e0, e1);
     case GEMM_LM:
         return launch_gemm_t<P, kLmTiles, RG, E_ARGMAX>(p, row_tiles, s, e0, e1);
