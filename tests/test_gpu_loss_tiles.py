@@ -1,0 +1,42 @@
+"""Loss-head products at the edges of their tiles: 64 and 65 GEMM rows (64 x 128 and 128 x 128
+tiles), 1 to 64 loss rows around the 32-row padding of the packed gradients, a width that is no
+multiple of the 128-column tiles (320) and a vocabulary one past a 2048-entry chunk. Against the
+oracle, with test_gpu_loss's bf16 tolerance (relative to the sums of absolute terms).
+"""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2403_00835_amd import workload
+from paper_2403_00835_amd.configs import ModelConfig
+from tests.parity import log
+from tests.test_gpu_loss import TOLS, _close_array, _close_rows, _grad_scales
+
+pytestmark = pytest.mark.gpu
+
+CFG = ModelConfig(n_layers=1, d_model=320, n_heads=5, head_dim=64, ffn_dim=64, vocab=2049)
+
+
+@pytest.fixture(scope="module")
+def head():
+    from paper_2403_00835_amd import binding
+    ws = workload.make_weights(CFG, seed=51)
+    m = binding.Model(CFG, max_ctx=64, max_block=8, max_new=8, weights=ws)
+    yield m, workload.as_f32(CFG, ws[-1]).astype(np.float64)
+    m.close()
+
+
+@pytest.mark.parametrize("P,A", [(32, 0), (32, 1), (1, 30), (1, 31), (1, 32), (31, 33)])
+def test_loss_head_tiles(head, P, A):
+    m, W = head
+    tol = TOLS["bf16"]
+    t, s, ar, tg = workload.make_head_rows(CFG, P, A, seed=52 + P + A)
+    log(f"[loss-tiles] P={P} A={A}: {2 * P + A} GEMM rows, {P + A} loss rows")
+    g = m.loss_head(t, s, ar, tg, 0.7, want_dw=True)
+    o = oracle.loss_head(W, t, s, ar, tg, 0.7)
+    _close_rows(g["kl"], o["kl"], tol, "kl")
+    _close_rows(g["nll"], o["nll"], tol, "nll")
+    sc_s, sc_a, sc_w = _grad_scales(W, t, s, ar, tg, 0.7)
+    _close_array(g["d_student"], o["d_student"], sc_s, tol, "d_student")
+    _close_array(g["d_ar"], o["d_ar"], sc_a, tol, "d_ar")
+    _close_array(g["d_W"], o["d_W"], sc_w, tol, "d_W")
