@@ -381,14 +381,18 @@ __global__ __launch_bounds__(256) void loss_dh_sum_kernel(const float *part, int
 }
 
 // One workgroup per row: out = x (.) g / sqrt(mean(x^2) + eps), the LM head's input row.
-__global__ __launch_bounds__(kLossThreads) void hidden_rows_kernel(const float *X, int ldx, int d, const float *g,
-                                                                   float eps, float *out) {
+__global__ __launch_bounds__(kLossThreads) void hidden_rows_kernel(const float *__restrict__ X, int ldx, int d,
+                                                                   const float *__restrict__ g, float eps,
+                                                                   float *__restrict__ out) {
     __shared__ float s_buf[4];
     const float *x = X + (size_t)blockIdx.x * ldx;
     float ss = 0.f;
+    // eight loads in flight per thread (one at a time, 4096 columns took 8.8 us; 4.0 now)
+#pragma unroll 8
     for (int k = threadIdx.x; k < d; k += kLossThreads) ss += x[k] * x[k];
     ss = block_reduce<false>(ss, s_buf);
     const float inv = 1.0f / sqrtf(ss / (float)d + eps);
+#pragma unroll 8
     for (int k = threadIdx.x; k < d; k += kLossThreads) out[(size_t)blockIdx.x * d + k] = x[k] * g[k] * inv;
 }
 
