@@ -63,7 +63,7 @@ struct GemmParams {
     // E_SWIGLU
     void *H;
     int Fp;
-    // E_ARGMAX: per-workgroup (max, index) [workgroup][row capacity]; optional logits [row][V]
+    // E_ARGMAX: per-workgroup (max, index) [row][workgroup]; optional logits [row][V]
     float *pmax;
     int *pidx;
     float *dbg;

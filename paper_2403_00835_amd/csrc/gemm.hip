@@ -237,8 +237,9 @@ __device__ __forceinline__ void gemm_epilogue(const GemmParams &p, float *s_tile
                 if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
             }
             if (lane == 0) {
-                p.pmax[(size_t)wg * p.rr.cap + row0 + row] = bv;
-                p.pidx[(size_t)wg * p.rr.cap + row0 + row] = nan ? -1 : bi;
+                const size_t o = (size_t)(row0 + row) * ((p.cols + COLS - 1) / COLS) + wg;  // [row][column workgroup]
+                p.pmax[o] = bv;
+                p.pidx[o] = nan ? -1 : bi;
             }
         }
     }
@@ -709,7 +710,7 @@ __global__ __launch_bounds__(kGemmWaves * kWave, 2) void gemm_prompt_kernel(Gemm
 
 // ------------------------------------------------------------------------------------------
 // Row-tiled decode GEMM (iterations of more than 64 rows, bf16): workgroup tiles of 64 rows x
-// 16 NT columns with the operand blocks brought into LDS by DMA (as gemm_prompt_dma_kernel, NB
+// 16 NT columns with the operand blocks brought into LDS by DMA (as gemm_prompt_kernel, NB
 // buffers, NB - 1 k-steps in flight) and gemm_kernel's reduction order, so that every row gets
 // the bits a one-tile iteration gives it (batched, AR and Jacobi decoding stay bit-identical):
 // k-step k is accumulated into the set of its class k % 8 (from zero, the hi then the lo MFMA, in

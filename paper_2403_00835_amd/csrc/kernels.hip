@@ -880,8 +880,9 @@ __device__ void commit_scalar(Ctl *c, int m, int a, int err, int32_t *mlog, int3
 }
 
 // One workgroup per batch entry: the final argmax of each of its rows over the LM-head
-// workgroups (16 threads per row take strided workgroups, then a 16-way tree; (max, lowest id)
-// is exact, so the order is free); the accepted length (a = 1 + the leading k >= 1 with
+// workgroups (one wave per row, (max, lowest id) is exact, so the order is free; the partials of a
+// row are contiguous: strided by the row capacity, each was a cache line of its own and a row of
+// 500 took four rounds of loads, 11.3 us for one row, 6.6 now); the accepted length (a = 1 + the leading k >= 1 with
 // z[k] = pred[k-1], from one wave's ballot); the emitted tokens; the state update (one thread);
 // the next block's tokens (one thread per position). The sequence's control block is worked on
 // in LDS (one parallel copy in, one out), so the state update is not a chain of global-memory
@@ -916,48 +917,64 @@ __global__ __launch_bounds__(1024) void scan_commit_kernel(ScanParams p) {
             const bool prefill = gc->mode == MODE_PREFILL;
             const int nrows = prefill ? 1 : m;            // <= 64
             const int rbase = r0 + (prefill ? m - 1 : 0);
-            const int row = tid & 63, j = tid >> 6;
-            float bv = -INFINITY;
-            int bx = 0x7fffffff;
-            int nan = 0;
-            if (row < nrows) {
-                for (int g0 = j; g0 < p.n_wg; g0 += 16 * 8) {
-                    float v[8];
-                    int ix[8];
+            // Row r's partials are contiguous: wave w takes rows w, w + 16, ... with the loads of all its
+            // rows (at most four) and eight column workgroups per lane in flight at once.
+            const int w = tid >> 6, lane = tid & 63;
+            float bv[4];
+            int bx[4], nan[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                bv[q] = -INFINITY;
+                bx[q] = 0x7fffffff;
+                nan[q] = 0;
+            }
+            for (int g0 = lane; g0 < p.n_wg; g0 += kWave * 8) {
+                float v[4][8];
+                int ix[4][8];
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
 #pragma unroll
                     for (int u = 0; u < 8; ++u) {
-                        const int g = g0 + 16 * u;
-                        ix[u] = g < p.n_wg ? p.pidx[(size_t)g * p.cap + rbase + row] : 0x7fffffff;
-                        v[u] = g < p.n_wg ? p.pmax[(size_t)g * p.cap + rbase + row] : -INFINITY;
+                        const int g = g0 + kWave * u;
+                        const bool in = w + 16 * q < nrows && g < p.n_wg;
+                        const size_t o = (size_t)(rbase + w + 16 * q) * p.n_wg + g;
+                        ix[q][u] = in ? p.pidx[o] : 0x7fffffff;
+                        v[q][u] = in ? p.pmax[o] : -INFINITY;
                     }
 #pragma unroll
+                for (int q = 0; q < 4; ++q)
+#pragma unroll
                     for (int u = 0; u < 8; ++u) {
-                        if (ix[u] < 0) nan = 1;
-                        else if (v[u] > bv || (v[u] == bv && ix[u] < bx)) { bv = v[u]; bx = ix[u]; }
+                        if (ix[q][u] < 0) nan[q] = 1;
+                        else if (v[q][u] > bv[q] || (v[q][u] == bv[q] && ix[q][u] < bx[q])) {
+                            bv[q] = v[q][u];
+                            bx[q] = ix[q][u];
+                        }
+                    }
+            }
+            __shared__ int s_arg[kMaxBlock];  // the row's argmax, -1 after a NaN
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                if (w + 16 * q >= nrows) break;  // uniform over the wave
+#pragma unroll
+                for (int off = 32; off >= 1; off >>= 1) {
+                    const float ov = __shfl_xor(bv[q], off);
+                    const int oi = __shfl_xor(bx[q], off);
+                    nan[q] |= __shfl_xor(nan[q], off);
+                    if (ov > bv[q] || (ov == bv[q] && oi < bx[q])) {
+                        bv[q] = ov;
+                        bx[q] = oi;
                     }
                 }
+                if (lane == 0) s_arg[w + 16 * q] = nan[q] || bx[q] == 0x7fffffff ? -1 : bx[q];
             }
-            __shared__ float s_v[1024];
-            __shared__ int s_i[1024];
-            __shared__ int s_nan[1024];
-            s_v[tid] = bv;
-            s_i[tid] = bx;
-            s_nan[tid] = nan;
             __syncthreads();
             // this iteration's trajectory record (decode loops with recording on)
             int32_t *rec = (p.trace && c->mode == MODE_DECODE && c->steps < p.trace_cap)
                                ? p.trace + ((size_t)seq * p.trace_cap + c->steps) * kTraceStride
                                : nullptr;
             if (tid < nrows) {
-                float best = s_v[tid];
-                int i = s_i[tid], nn = s_nan[tid];
-                for (int jj = 1; jj < 16; ++jj) {
-                    const float ov = s_v[jj * 64 + tid];
-                    const int oi = s_i[jj * 64 + tid];
-                    nn |= s_nan[jj * 64 + tid];
-                    if (ov > best || (ov == best && oi < i)) { best = ov; i = oi; }
-                }
-                const int pr = (nn || i == 0x7fffffff) ? -1 : i;
+                const int pr = s_arg[tid];
                 c->pred[tid] = pr;
                 s_pred[tid] = pr;
                 if (rec) {
