@@ -1013,11 +1013,20 @@ cllm_status loss_head_enqueue(cllm_ctx *c, const float *T, const float *S, int P
     const int nch = ceil_div(Vp, kLossChunk);
     const int rpad = round_up(Rg, 32);
     const int kstep = c->bf16 ? 32 : 16;  // MFMA k-step (elements)
-    // dH splits over the vocabulary's k-steps: one workgroup per CU over the columns of d (bf16, 128
-    // columns each), about 512 smaller ones (fp32)
-    const int ks_v = Vp / kstep, n_wg_dh = ceil_div(d, c->bf16 ? 128 : 16 * kLmTiles);
-    const int want = c->bf16 ? kCUs / n_wg_dh : ceil_div(512, n_wg_dh);
-    const int kc = ceil_div(ks_v, std::max(1, std::min(ks_v, want)));
+    // dH splits over the vocabulary's k-steps: about 512 workgroups of 64 columns of d (two per CU).
+    // The bf16 kernel runs one workgroup of 128 columns per CU: where these ranges would leave the
+    // last round of the CUs mostly empty (d 5120: 7 x 40 workgroups, 203 us a call), the fewest that
+    // are no longer and fill whole rounds (12 x 40, 177 us). The ranges are part of a sum's order, so
+    // they depend on the model's shape only.
+    const int ks_v = Vp / kstep, n_wg_dh = ceil_div(d, 16 * kLmTiles);
+    int kc = ceil_div(ks_v, std::max(1, std::min(ks_v, ceil_div(512, n_wg_dh))));
+    if (c->bf16) {
+        const int n_wg = ceil_div(d, 128), longest = kc;
+        for (int wgs = kCUs;; wgs += kCUs) {
+            kc = ceil_div(ks_v, std::min(ks_v, wgs / n_wg));  // n_wg <= kCUs
+            if (kc <= longest) break;
+        }
+    }
     const int nsplit = ceil_div(ks_v, kc);
     auto &w = c->loss;
     cllm_status s;
@@ -1078,7 +1087,7 @@ cllm_status loss_head_enqueue(cllm_ctx *c, const float *T, const float *S, int P
         HIPCHK(c, launch_loss_grad_pack(lp, w.stats, kMaxRows, reinterpret_cast<uint16_t *>(w.Dact), rpad, w.DT, st, e1));
     else
         HIPCHK(c, launch_loss_grad_f32(lp, w.stats, kMaxRows, reinterpret_cast<float *>(w.Dact), st, e1));
-    // dH = D W: the streaming GEMM over the transposed LM head, K (the vocabulary) split nsplit ways
+    // dH = D W over the transposed LM head, K (the vocabulary) split nsplit ways
     GemmParams h{};
     h.W = w.WT;
     h.Ks = ks_v;

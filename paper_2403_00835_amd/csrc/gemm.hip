@@ -431,16 +431,21 @@ template <int NT, int WM, int EP>
 __host__ __device__ constexpr int prompt_row_floats() {
     return (EP == E_SWIGLU ? 8 : 16) * (NT / (kGemmWaves / WM)) + 4;
 }
-template <int NT, int RG, int WM, int EP, int NB>
+template <int NT, int RG, int WM, int EP, int NB, bool CLS = false>
 __host__ __device__ constexpr int prompt_lds_bytes() {
-    constexpr int stage = NB * (2 * RG + NT) * kTileBytes;
+    constexpr int stage = NB * (2 * RG + NT) * kTileBytes + (CLS && RG == 8 ? 16 * RG * 16 * NT * 4 : 0);
     constexpr int after = (kGemmWaves * (16 * RG / WM) * prompt_row_floats<NT, WM, EP>() + 16 * RG) * 4;
     return stage > after ? stage : after;
 }
 
-// NA = 2 keeps the even and the odd k-steps' sums apart and adds them at the end: chains half as
-// long, for the loss head's products, whose fp32 results are compared with 64 bits as they are.
-template <int NT, int RG, int WM, int EP, int NB, int NA = 1>
+// CLS keeps gemm_kernel's reduction order instead: one accumulator per class of k-steps (k % 8), added
+// in its tree ((0+4)+(2+6))+((1+5)+(3+7)) at the end. For the loss head's products, whose fp32 results
+// leave the library as they are: a single chain is 3-6% further from 64 bits at the 7B head. Eight
+// accumulators of a 128 x 128 tile do not fit the registers, so it takes the even k-steps first, then
+// the odd ones (four classes each; the weights are stored k-step by k-step, so the order of the
+// visits costs nothing), with the even classes' sum held in LDS behind the ring meanwhile. (One
+// accumulator and a fold after each class in turn: 3-4 us more a launch in register moves.)
+template <int NT, int RG, int WM, int EP, int NB, bool CLS = false>
 __global__ __launch_bounds__(kGemmWaves * kWave, 2) void gemm_prompt_kernel(GemmParams p) {
     constexpr Prec P = Prec::BF16;
     constexpr int W = kGemmWaves, WN = W / WM, RGW = RG / WM, NTW = NT / WN;
@@ -516,26 +521,35 @@ __global__ __launch_bounds__(kGemmWaves * kWave, 2) void gemm_prompt_kernel(Gemm
         }
         src[i] += (size_t)ks0 * adv[i];  // the first k-step of this workgroup's K range
     }
-    // k-step s into ring buffer buf; past the last k-step a harmless reload of it
-    auto issue = [&](int s, int buf) {
-        const size_t ss = (size_t)min(s, Ks - 1);
+    // The next k-step of the order into ring buffer buf; past the last one a harmless reload of it.
+    // With two passes the first one is padded to whole turns of the accumulators.
+    constexpr int PASSES = CLS && RG == 8 ? 2 : 1, SETS = CLS ? 8 / PASSES : 1;
+    int kn = 0;  // the next k-step to issue
+    const int kodd = (((Ks + 1) >> 1) + SETS - 1) / SETS * SETS * 2;  // where the odd k-steps follow
+    auto issue = [&](int buf) {
+        const size_t ss = (size_t)min(kn, Ks - 1);
         u32x4 *bb = s_stage + (size_t)buf * BLK * kWave;
 #pragma unroll
         for (int i = 0; i < NLW; ++i)
             __builtin_amdgcn_global_load_lds(static_cast<const void *>(src[i] + ss * adv[i]),
                                              (__attribute__((address_space(3))) void *)(bb + (size_t)dst[i] * kWave), 16,
                                              0, 0);
+        kn += PASSES;
+        if (PASSES == 2 && kn == kodd) kn = 1;
     };
 #pragma unroll
-    for (int q = 0; q < NB - 1; ++q) issue(q, q);
+    for (int q = 0; q < NB - 1; ++q) issue(q);
 
-    f32x4 accs[NA][RGW][NTW];
+    f32x4 accs[SETS][RGW][NTW];
+    auto clear = [&]() {
 #pragma unroll
-    for (int q = 0; q < NA; ++q)
+        for (int q = 0; q < SETS; ++q)
 #pragma unroll
-        for (int r = 0; r < RGW; ++r)
+            for (int r = 0; r < RGW; ++r)
 #pragma unroll
-            for (int j = 0; j < NTW; ++j) accs[q][r][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+                for (int j = 0; j < NTW; ++j) accs[q][r][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    };
+    clear();
     u32x4 a[2][2][RGW], b[2][NTW];  // two sets: the k-step being computed, the next one
     auto read_operands = [&](auto set, int buf) {
         constexpr int st = decltype(set)::value;
@@ -547,21 +561,22 @@ __global__ __launch_bounds__(kGemmWaves * kWave, 2) void gemm_prompt_kernel(Gemm
 #pragma unroll
             for (int r = 0; r < RGW; ++r) a[st][pl][r] = bp[(pl * RG + wm * RGW + r) * kWave];
     };
-    int rbuf = 1, ibuf = NB - 1;  // ring buffers of k-steps s + 1 and s + NB - 1
-    auto step = [&](auto set, int s) {
-        constexpr int st = decltype(set)::value;
-        wait_vm_lds<(NB - 3) * NLW>();  // this wave's blocks of k-step s + 1 have landed
+    int rbuf = 1, ibuf = NB - 1;  // ring buffers of the next k-step and of the one NB - 1 ahead
+    auto step = [&](auto set, auto which, bool add = true) {  // operand set, accumulator set
+        constexpr int st = decltype(set)::value, ac = decltype(which)::value;
+        wait_vm_lds<(NB - 3) * NLW>();  // this wave's blocks of the next k-step have landed
         barrier_no_fence();             // every wave's; buffer ibuf has no reader left
-        issue(s + NB - 1, ibuf);
+        issue(ibuf);
         if (live) {
             read_operands(std::integral_constant<int, st ^ 1>{}, rbuf);
+            if (add) {
 #pragma unroll
-            for (int pl = 0; pl < 2; ++pl)
+                for (int pl = 0; pl < 2; ++pl)
 #pragma unroll
-                for (int r = 0; r < RGW; ++r)
+                    for (int r = 0; r < RGW; ++r)
 #pragma unroll
-                    for (int j = 0; j < NTW; ++j)
-                        accs[st % NA][r][j] = mfma_kstep<P>(a[st][pl][r], b[st][j], accs[st % NA][r][j]);
+                        for (int j = 0; j < NTW; ++j) accs[ac][r][j] = mfma_kstep<P>(a[st][pl][r], b[st][j], accs[ac][r][j]);
+            }
             // schedule: one LDS read after every few MFMAs
             constexpr int reads = 2 * RGW + NTW, mfmas = 2 * RGW * NTW, per = mfmas >= reads ? mfmas / reads : 1;
 #pragma unroll
@@ -579,23 +594,90 @@ __global__ __launch_bounds__(kGemmWaves * kWave, 2) void gemm_prompt_kernel(Gemm
     wait_vm<(NB - 2) * NLW>();  // this wave's blocks of k-step 0
     barrier_no_fence();
     if (live) read_operands(set0, 0);
-    int s = 0;
-    for (; s + 2 <= Ks; s += 2) {
-        step(set0, s);
-        step(set1, s + 1);
+    auto &acc = accs[0];
+    if constexpr (CLS) {
+        constexpr std::integral_constant<int, 2> set2{};
+        constexpr std::integral_constant<int, 3> set3{};
+        constexpr std::integral_constant<int, 4> set4{};
+        constexpr std::integral_constant<int, 5> set5{};
+        constexpr std::integral_constant<int, 6> set6{};
+        constexpr std::integral_constant<int, 7> set7{};
+        auto add = [&](int to, int from) {
+#pragma unroll
+            for (int r = 0; r < RGW; ++r)
+#pragma unroll
+                for (int j = 0; j < NTW; ++j)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) accs[to][r][j][e] += accs[from][r][j][e];
+        };
+        if constexpr (PASSES == 1) {
+            int n = Ks;
+            for (; n >= SETS; n -= SETS) {
+                step(set0, set0);
+                step(set1, set1);
+                step(set0, set2);
+                step(set1, set3);
+                step(set0, set4);
+                step(set1, set5);
+                step(set0, set6);
+                step(set1, set7);
+            }
+            if (n > 0) step(set0, set0);
+            if (n > 1) step(set1, set1);
+            if (n > 2) step(set0, set2);
+            if (n > 3) step(set1, set3);
+            if (n > 4) step(set0, set4);
+            if (n > 5) step(set1, set5);
+            if (n > 6) step(set0, set6);
+            add(0, 4), add(2, 6), add(1, 5), add(3, 7);
+            add(0, 2), add(1, 3);
+            add(0, 1);
+        } else {  // classes 0 2 4 6, then 1 3 5 7
+            f32x4 *even = reinterpret_cast<f32x4 *>(s_stage + (size_t)NB * BLK * kWave) + tid;  // the lane's own places
+            for (int ps = 0; ps < 2; ++ps) {
+                const int n = (Ks + 1 - ps) >> 1;
+                int g = 0;
+                for (; g + SETS <= n; g += SETS) {
+                    step(set0, set0);
+                    step(set1, set1);
+                    step(set0, set2);
+                    step(set1, set3);
+                }
+                if (g < n) {  // the last turn, padded
+                    step(set0, set0);
+                    step(set1, set1, g + 1 < n);
+                    step(set0, set2, g + 2 < n);
+                    step(set1, set3, false);
+                }
+                add(0, 2), add(1, 3);
+                add(0, 1);
+                if (ps == 0) {
+#pragma unroll
+                    for (int r = 0; r < RGW; ++r)
+#pragma unroll
+                        for (int j = 0; j < NTW; ++j) even[(r * NTW + j) * W * kWave] = acc[r][j];
+                    clear();
+                }
+            }
+#pragma unroll
+            for (int r = 0; r < RGW; ++r)
+#pragma unroll
+                for (int j = 0; j < NTW; ++j) {
+                    const f32x4 x = even[(r * NTW + j) * W * kWave];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[r][j][e] = x[e] + acc[r][j][e];
+                }
+        }
+    } else {
+        int s = 0;
+        for (; s + 2 <= Ks; s += 2) {
+            step(set0, set0);
+            step(set1, set0);
+        }
+        if (s < Ks) step(set0, set0);
     }
-    if (s < Ks) step(set0, s);
     wait_vm<0>();  // the trailing reloads have landed before the buffers are reused
     __syncthreads();
-    auto &acc = accs[0];
-    if constexpr (NA == 2) {
-#pragma unroll
-        for (int r = 0; r < RGW; ++r)
-#pragma unroll
-            for (int j = 0; j < NTW; ++j)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) acc[r][j][e] += accs[NA - 1][r][j][e];
-    }
 
     // The wave's outputs into its LDS block (C layout of a 16 x 16 tile: lane l, register v -> row
     // 4 (l / 16) + v, column l % 16), then out as vectors.
@@ -1362,18 +1444,18 @@ hipError_t launch_gemm_prompt(GemmKind kind, int rows, const GemmParams &p, hipS
 
 // Plain fp32 product of a few rows (the loss head's logits and dH, bf16): the prompt kernel's
 // tiles over `rows` <= 128 rows, with p.kc > 0 as K ranges into planes of p.Zout.
-template <int NT, int RG, int WM>
+template <int NT, int RG, int WM, int NB>
 static hipError_t launch_rows_product_t(const GemmParams &p, int rows, int splits, hipStream_t s, hipEvent_t e0,
                                         hipEvent_t e1) {
-    constexpr int ROWS = 16 * RG, COLS = 16 * NT, NB = 5;
-    constexpr size_t lds = (size_t)prompt_lds_bytes<NT, RG, WM, E_LOGITS, NB>();
+    constexpr int ROWS = 16 * RG, COLS = 16 * NT;
+    constexpr size_t lds = (size_t)prompt_lds_bytes<NT, RG, WM, E_LOGITS, NB, true>();
     static_assert(lds <= 160 * 1024, "the LDS of a CU");
     if (p.rr.cap % ROWS != 0) return hipErrorInvalidValue;
     GemmParams q = p;
     q.n_wg = (p.cols + COLS - 1) / COLS;
     q.row_tiles = (rows + ROWS - 1) / ROWS;
     const dim3 grid((unsigned)((q.n_wg + 7) / 8 * 8 * q.row_tiles), (unsigned)splits);
-    auto kern = gemm_prompt_kernel<NT, RG, WM, E_LOGITS, NB, 2>;
+    auto kern = gemm_prompt_kernel<NT, RG, WM, E_LOGITS, NB, true>;
     if (e0 || e1)
         hipExtLaunchKernelGGL(kern, grid, dim3(kGemmWaves * kWave), lds, s, e0, e1, 0, q);
     else
@@ -1381,16 +1463,18 @@ static hipError_t launch_rows_product_t(const GemmParams &p, int rows, int split
     return hipGetLastError();
 }
 
-// Up to 64 rows take 64 x 128 tiles and up to 128 rows 128 x 128 tiles: the head's 32000 columns
-// are then 250 workgroups, one round of the CUs, and the head is streamed once for all rows (two
-// launches of gemm_kernel, one per 64-row tile, took 104 us for 80 rows of the 7B head).
+// Up to 64 rows take 64 x 128 tiles and up to 128 rows 128 x 128 tiles: the 7B head's 32000 columns are
+// then 250 workgroups, one round of the CUs, and the head is streamed once for all rows (two launches
+// of gemm_kernel, one per 64-row tile, took 104 us for 80 rows of it). The class accumulators cost
+// 3% of a whole call at 65 to 128 rows (loss and gradients of 16 pairs and 48 AR rows without dW: 169
+// -> 174 us) and up to 2% below.
 hipError_t launch_rows_product(int rows, const GemmParams &p, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
     if (rows < 1 || rows > 128 || rows > p.rr.cap || p.lda % 32 != 0 || p.cols % 16 != 0 || p.Ks < 1 || p.kc < 0 ||
         !p.Zout || p.ldz < p.cols || p.ldz % 4 != 0 || p.zstride % 4 != 0)
         return hipErrorInvalidValue;
     const int splits = p.kc > 0 ? (p.Ks + p.kc - 1) / p.kc : 1;
-    if (rows <= 64) return launch_rows_product_t<8, 4, 2>(p, rows, splits, s, e0, e1);
-    return launch_rows_product_t<8, 8, 2>(p, rows, splits, s, e0, e1);
+    if (rows <= 64) return launch_rows_product_t<8, 4, 2, 5>(p, rows, splits, s, e0, e1);
+    return launch_rows_product_t<8, 8, 2, 4>(p, rows, splits, s, e0, e1);
 }
 
 // Grid: column workgroups (ceil(p.cols / (16 * NT))) x row tiles of 16 * RG rows (from row tile

@@ -443,6 +443,48 @@ int check_main(int rows) {
                     d16 + d32, n);
         bad += (d16 + d32) != 0;
     }
+    // the loss head's products (up to 128 rows): as the library launches them and through gemm_kernel,
+    // one launch per 64-row tile; also K ranges, ragged columns and fewer k-steps than classes
+    const struct {
+        const char *name;
+        int cols, K, kc, max_rows;
+    } loss[] = {{"logits", kV, kD, 0, 128}, {"logits_k13", 320, 416, 0, 128}, {"logits_k5", 192, 160, 0, 128},
+                {"dh", kD, kFp, 43, 64}, {"dh_ragged", 320, kFp, 7, 64}};
+    for (const auto &pr : loss) {
+        if (rows > pr.max_rows) continue;
+        GemmParams p{};
+        p.W = reinterpret_cast<const uint8_t *>(W);
+        p.Ks = pr.K / 32;
+        p.cols = pr.cols;
+        p.A = pr.K > kD ? A_f : A_d;
+        p.lda = pr.K;
+        p.rr = RowsRef{tab, nullptr, cap};
+        p.V = pr.cols;
+        p.Zout = spart;
+        p.ldz = pr.cols;
+        p.kc = pr.kc;
+        const int planes = pr.kc > 0 ? (p.Ks + pr.kc - 1) / pr.kc : 1;
+        p.zstride = pr.kc > 0 ? (size_t)rows * pr.cols : 0;
+        const size_t n = (size_t)planes * rows * pr.cols;
+        std::vector<float> out[2];
+        for (int way = 0; way < 2; ++way) {
+            CK(hipMemset(spart, 0, n * 4));
+            if (way == 0) {
+                CK(launch_rows_product(rows, p, 0, nullptr, nullptr));
+            } else {
+                for (int t = 0; t * kMaxRows < rows; ++t) {
+                    GemmParams q = p;
+                    q.rt0 = t;
+                    CK(launch_gemm(GEMM_LOGITS, true, 4, 1, q, 0, nullptr, nullptr));
+                }
+            }
+            CK(hipDeviceSynchronize());
+            out[way] = to_host(spart, n);
+        }
+        const size_t differ = count_diff(out[0], out[1]);
+        std::printf("check %-10s rows=%d: %zu of %zu output values differ\n", pr.name, rows, differ, n);
+        bad += differ != 0;
+    }
     std::printf(bad ? "check FAILED\n" : "check ok\n");
     return bad ? 1 : 0;
 }

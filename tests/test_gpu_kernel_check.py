@@ -8,7 +8,9 @@ rows, next RMSNorm operand and its sums of squares, SwiGLU rows, argmax partials
 bit-identical, from one 16-row group to eight 64-row tiles, ragged tails included (a one-tile
 launch and the last tile of a split launch run only their live 16-row groups, 1 to 4 of them): the
 split and the row-tiled kernels keep gemm_kernel's reduction order, which is what makes batched,
-Jacobi and AR decoding give the same bits for a row."""
+Jacobi and AR decoding give the same bits for a row. The loss head's products (up to 128 rows: the
+logits, dH's K ranges, ragged columns, fewer k-steps than classes) keep that order too, so that their
+fp32 results are no further from 64 bits than its chains make them."""
 import os
 import subprocess
 
@@ -20,7 +22,7 @@ from tests.parity import log
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("rows", [16, 17, 33, 48, 64, 65, 96, 120, 160, 200, 289, 512])
+@pytest.mark.parametrize("rows", [1, 16, 17, 32, 33, 48, 64, 65, 96, 120, 128, 160, 200, 289, 512])
 def test_multi_row_gemms_bit_identical(rows):
     exe = build.KERNEL_BENCH
     if not os.path.exists(exe):
@@ -30,3 +32,4 @@ def test_multi_row_gemms_bit_identical(rows):
     for line in r.stdout.splitlines():
         log("  " + line)
     assert r.returncode == 0 and "check ok" in r.stdout, r.stdout + r.stderr
+    assert ("check logits " in r.stdout) == (rows <= 128) and ("check dh " in r.stdout) == (rows <= 64)
