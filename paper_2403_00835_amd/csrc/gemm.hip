@@ -1468,10 +1468,21 @@ static hipError_t launch_rows_product_t(const GemmParams &p, int rows, int split
 // of gemm_kernel, one per 64-row tile, took 104 us for 80 rows of it). The class accumulators cost
 // 3% of a whole call at 65 to 128 rows (loss and gradients of 16 pairs and 48 AR rows without dW: 169
 // -> 174 us) and up to 2% below.
+//
+// Few rows take gemm_kernel, which skips the row groups that hold none and has two workgroups per CU
+// to hide a short row's latency; a 64-row tile reads and multiplies its padding (one pair, whole
+// call, tile against gemm_kernel: 7B head 133 -> 117 us, vocabulary 128256 420 -> 359, 8192 x 2048
+// 58 -> 51). The logits change over above 16 rows (20 rows: 127 us in tiles, 132 with gemm_kernel),
+// dH's K ranges, whose workgroups are shorter, above 32 (20 rows: 136 with gemm_kernel, 138 in tiles;
+// above 32 gemm_kernel is 5-9% slower).
+constexpr int kFewRows = 16, kFewRowsSplit = 32;
+
 hipError_t launch_rows_product(int rows, const GemmParams &p, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
     if (rows < 1 || rows > 128 || rows > p.rr.cap || p.lda % 32 != 0 || p.cols % 16 != 0 || p.Ks < 1 || p.kc < 0 ||
         !p.Zout || p.ldz < p.cols || p.ldz % 4 != 0 || p.zstride % 4 != 0)
         return hipErrorInvalidValue;
+    if (rows <= (p.kc > 0 ? kFewRowsSplit : kFewRows))
+        return launch_gemm(GEMM_LOGITS, true, rows <= 16 ? 1 : 2, 1, p, s, e0, e1);
     const int splits = p.kc > 0 ? (p.Ks + p.kc - 1) / p.kc : 1;
     if (rows <= 64) return launch_rows_product_t<8, 4, 2, 5>(p, rows, splits, s, e0, e1);
     return launch_rows_product_t<8, 8, 2, 4>(p, rows, splits, s, e0, e1);
