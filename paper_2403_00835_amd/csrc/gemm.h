@@ -96,8 +96,8 @@ hipError_t launch_gemm_prompt(GemmKind kind, int rows, const GemmParams &p, hipS
 
 // Plain fp32 product of at most 128 rows (bf16), in gemm_kernel's reduction order (GEMM_LOGITS gives the
 // same bits): Zout[row][ldz], columns < cols; with kc > 0 grid planes of partial products over K
-// ranges of kc k-steps, zstride floats apart. The row capacity must be a multiple of 64 (of 128
-// above 64 rows).
+// ranges of kc k-steps, zstride floats apart. The row capacity must be at least the row tile (64, 96
+// or 128 rows).
 hipError_t launch_rows_product(int rows, const GemmParams &p, hipStream_t s, hipEvent_t e0, hipEvent_t e1);
 
 }  // namespace cllm

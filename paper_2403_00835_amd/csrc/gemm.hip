@@ -433,7 +433,7 @@ __host__ __device__ constexpr int prompt_row_floats() {
 }
 template <int NT, int RG, int WM, int EP, int NB, bool CLS = false>
 __host__ __device__ constexpr int prompt_lds_bytes() {
-    constexpr int stage = NB * (2 * RG + NT) * kTileBytes + (CLS && RG == 8 ? 16 * RG * 16 * NT * 4 : 0);
+    constexpr int stage = NB * (2 * RG + NT) * kTileBytes + (CLS && RG > 4 ? 16 * RG * 16 * NT * 4 : 0);
     constexpr int after = (kGemmWaves * (16 * RG / WM) * prompt_row_floats<NT, WM, EP>() + 16 * RG) * 4;
     return stage > after ? stage : after;
 }
@@ -441,7 +441,7 @@ __host__ __device__ constexpr int prompt_lds_bytes() {
 // CLS keeps gemm_kernel's reduction order instead: one accumulator per class of k-steps (k % 8), added
 // in its tree ((0+4)+(2+6))+((1+5)+(3+7)) at the end. For the loss head's products, whose fp32 results
 // leave the library as they are: a single chain is 3-6% further from 64 bits at the 7B head. Eight
-// accumulators of a 128 x 128 tile do not fit the registers, so it takes the even k-steps first, then
+// accumulators of a tile of more than 64 rows do not fit the registers, so it takes the even k-steps first, then
 // the odd ones (four classes each; the weights are stored k-step by k-step, so the order of the
 // visits costs nothing), with the even classes' sum held in LDS behind the ring meanwhile. (One
 // accumulator and a fold after each class in turn: 3-4 us more a launch in register moves.)
@@ -453,7 +453,7 @@ __global__ __launch_bounds__(kGemmWaves * kWave, 2) void gemm_prompt_kernel(Gemm
     static_assert(RG % WM == 0 && NT % WN == 0 && NB >= 4, "tile split, ring depth");
     static_assert(EP == E_QKV || EP == E_SWIGLU || EP == E_LOGITS, "the prompt products' epilogues");
     static_assert(EP != E_SWIGLU || NTW % 2 == 0, "a wave holds whole (gate, up) tile pairs");
-    static_assert(kWave % (16 * RGW) == 0, "QKV epilogue: a lane serves one row");
+    static_assert(EP != E_QKV || kWave % (16 * RGW) == 0, "QKV epilogue: a lane serves one row");
     constexpr bool ROWSCALE = EP != E_LOGITS;  // the product follows an RMSNorm
     constexpr int ROWS = 16 * RG, WROWS = 16 * RGW;
     // Workgroup L runs on XCD L % 8 (round-robin dispatch). Column group cg belongs to XCD cg % 8,
@@ -523,7 +523,7 @@ __global__ __launch_bounds__(kGemmWaves * kWave, 2) void gemm_prompt_kernel(Gemm
     }
     // The next k-step of the order into ring buffer buf; past the last one a harmless reload of it.
     // With two passes the first one is padded to whole turns of the accumulators.
-    constexpr int PASSES = CLS && RG == 8 ? 2 : 1, SETS = CLS ? 8 / PASSES : 1;
+    constexpr int PASSES = CLS && RG > 4 ? 2 : 1, SETS = CLS ? 8 / PASSES : 1;
     int kn = 0;  // the next k-step to issue
     const int kodd = (((Ks + 1) >> 1) + SETS - 1) / SETS * SETS * 2;  // where the odd k-steps follow
     auto issue = [&](int buf) {
@@ -1450,11 +1450,11 @@ static hipError_t launch_rows_product_t(const GemmParams &p, int rows, int split
     constexpr int ROWS = 16 * RG, COLS = 16 * NT;
     constexpr size_t lds = (size_t)prompt_lds_bytes<NT, RG, WM, E_LOGITS, NB, true>();
     static_assert(lds <= 160 * 1024, "the LDS of a CU");
-    if (p.rr.cap % ROWS != 0) return hipErrorInvalidValue;
+    if (rows > ROWS || p.rr.cap < ROWS) return hipErrorInvalidValue;
     GemmParams q = p;
     q.n_wg = (p.cols + COLS - 1) / COLS;
-    q.row_tiles = (rows + ROWS - 1) / ROWS;
-    const dim3 grid((unsigned)((q.n_wg + 7) / 8 * 8 * q.row_tiles), (unsigned)splits);
+    q.row_tiles = 1;
+    const dim3 grid((unsigned)((q.n_wg + 7) / 8 * 8), (unsigned)splits);
     auto kern = gemm_prompt_kernel<NT, RG, WM, E_LOGITS, NB, true>;
     if (e0 || e1)
         hipExtLaunchKernelGGL(kern, grid, dim3(kGemmWaves * kWave), lds, s, e0, e1, 0, q);
@@ -1463,11 +1463,12 @@ static hipError_t launch_rows_product_t(const GemmParams &p, int rows, int split
     return hipGetLastError();
 }
 
-// Up to 64 rows take 64 x 128 tiles and up to 128 rows 128 x 128 tiles: the 7B head's 32000 columns are
+// Up to 64, 96 and 128 rows take tiles of as many rows x 128 columns: the 7B head's 32000 columns are
 // then 250 workgroups, one round of the CUs, and the head is streamed once for all rows (two launches
 // of gemm_kernel, one per 64-row tile, took 104 us for 80 rows of it). The class accumulators cost
-// 3% of a whole call at 65 to 128 rows (loss and gradients of 16 pairs and 48 AR rows without dW: 169
-// -> 174 us) and up to 2% below.
+// 3-4% of a whole call in 128-row tiles, whose ring is then four buffers (7B head, 64 pairs without
+// dW: 176 -> 183 us), and up to 2% in 64-row ones. The 96-row tile, which holds five buffers, gives
+// that back (16 pairs and 48 AR rows: 170 us with one chain, 177 in a 128-row tile, 169 in a 96-row one).
 //
 // Few rows take gemm_kernel, which skips the row groups that hold none and has two workgroups per CU
 // to hide a short row's latency; a 64-row tile reads and multiplies its padding (one pair, whole
@@ -1485,6 +1486,7 @@ hipError_t launch_rows_product(int rows, const GemmParams &p, hipStream_t s, hip
         return launch_gemm(GEMM_LOGITS, true, rows <= 16 ? 1 : 2, 1, p, s, e0, e1);
     const int splits = p.kc > 0 ? (p.Ks + p.kc - 1) / p.kc : 1;
     if (rows <= 64) return launch_rows_product_t<8, 4, 2, 5>(p, rows, splits, s, e0, e1);
+    if (rows <= 96) return launch_rows_product_t<8, 6, 2, 5>(p, rows, splits, s, e0, e1);
     return launch_rows_product_t<8, 8, 2, 4>(p, rows, splits, s, e0, e1);
 }
 

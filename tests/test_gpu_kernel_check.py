@@ -22,7 +22,7 @@ from tests.parity import log
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("rows", [1, 16, 17, 32, 33, 48, 64, 65, 96, 120, 128, 160, 200, 289, 512])
+@pytest.mark.parametrize("rows", [1, 16, 17, 32, 33, 48, 64, 65, 96, 97, 120, 128, 160, 200, 289, 512])
 def test_multi_row_gemms_bit_identical(rows):
     exe = build.KERNEL_BENCH
     if not os.path.exists(exe):

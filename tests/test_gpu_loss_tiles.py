@@ -1,5 +1,5 @@
-"""Loss-head products at the edges of their tiles: 16, 17, 64 and 65 GEMM rows (gemm_kernel, 64 x 128
-and 128 x 128 tiles; dH changes over at 32 and 33 rows), 1 to 64 loss rows around the 32-row padding of the packed gradients, a width that is no
+"""Loss-head products at the edges of their tiles: 16, 17, 64, 65, 96 and 97 GEMM rows (gemm_kernel,
+tiles of 64, 96 and 128 rows; dH changes over at 32 and 33 rows), 1 to 64 loss rows around the 32-row padding of the packed gradients, a width that is no
 multiple of the 128-column tiles (320) and a vocabulary one past a 2048-entry chunk. Against the
 oracle, with test_gpu_loss's bf16 tolerance (relative to the sums of absolute terms).
 """
@@ -26,7 +26,7 @@ def head():
     m.close()
 
 
-@pytest.mark.parametrize("P,A", [(32, 0), (32, 1), (1, 30), (1, 31), (1, 32), (31, 33), (1, 0), (8, 0), (0, 17)])
+@pytest.mark.parametrize("P,A", [(32, 0), (32, 1), (1, 30), (1, 31), (1, 32), (31, 33), (1, 0), (8, 0), (0, 17), (48, 0), (48, 1)])
 def test_loss_head_tiles(head, P, A):
     m, W = head
     tol = TOLS["bf16"]
