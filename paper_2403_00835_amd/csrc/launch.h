@@ -101,14 +101,15 @@ struct LossParams {
     float *D;          // fp32: logit gradients [P + A][ldz] (student rows, then AR rows; 0 past V)
 };
 // Per-row losses and logit gradients in two passes over vocabulary chunks of kLossChunk entries:
-// per-chunk statistics (stats: [P + A][chunks][5] floats), then their combination in chunk order,
+// per-chunk statistics (stats: [P + A][chunks][5] floats; a large vocabulary's are folded in place),
+// then their combination in chunk order,
 // the losses and the gradients: as operands of the next products (bf16: Dact, the GEMM operand of
 // dH = D W, row capacity cap, K = ldz; DT, that of dW = D^T H with the contraction over rpad rows, two
 // planes of ldz x rpad, zero rows from P + A on), or (fp32) as p.D and Dact. e0 marks the start of
 // the first pass, e1 the end of the last launch.
 constexpr int kLossChunk = 2048;
 hipError_t launch_loss_stats(const LossParams &p, float *stats, hipStream_t s, hipEvent_t e0);
-hipError_t launch_loss_grad_pack(const LossParams &p, const float *stats, int cap, uint16_t *Dact, int rpad, uint16_t *DT,
+hipError_t launch_loss_grad_pack(const LossParams &p, float *stats, int cap, uint16_t *Dact, int rpad, uint16_t *DT,
                                  hipStream_t s, hipEvent_t e1);
 hipError_t launch_loss_grad_f32(const LossParams &p, const float *stats, int cap, float *Dact, hipStream_t s, hipEvent_t e1);
 // Rows (fp32 [.][d]: np teacher rows T0, np student rows S0, na AR rows R0, in that order) to the

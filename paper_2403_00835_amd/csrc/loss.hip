@@ -203,6 +203,62 @@ __global__ __launch_bounds__(256) void pack_inputs_kernel(const float *T0, const
     *reinterpret_cast<u32x4 *>(HT + (size_t)d * rpad + o) = l;
 }
 
+// The statistics of n chunks folded in chunk order (pair: student logits and the cross term too).
+__device__ __forceinline__ void fold_max(const float *st, int n, bool pair, float &ma, float &ms) {
+    for (int k = 0; k < n; ++k) {
+        ma = fmaxf(ma, st[k * kStat + 0]);
+        if (pair) ms = fmaxf(ms, st[k * kStat + 3]);
+    }
+}
+__device__ __forceinline__ void fold_sum(const float *st, int n, bool pair, float ma, float ms, float &za, float &zs,
+                                         float &cross) {
+    for (int k = 0; k < n; ++k) {
+        const float fa = expf(st[k * kStat + 0] - ma);
+        za += st[k * kStat + 1] * fa;
+        if (pair) {
+            cross += st[k * kStat + 2] * fa;
+            zs += st[k * kStat + 4] * expf(st[k * kStat + 3] - ms);
+        }
+    }
+}
+
+// Row b's loss from its folded statistics.
+__device__ __forceinline__ void write_loss(const LossParams &p, int b, float ma, float ms, float za, float zs, float cross) {
+    if (b < p.P) {
+        // KL(p || q) = sum_v p_v (a_v - s_v) - logsumexp(a) + logsumexp(s)
+        p.kl[b] = cross / za - (ma + logf(za)) + (ms + logf(zs));
+    } else {
+        const int i = b - p.P, t = p.targets[i];
+        // a target outside the vocabulary: NaN
+        p.nll[i] = t < 0 || t >= p.V ? NAN : ma + logf(za) - p.Z[(size_t)(2 * p.P + i) * p.ldz + t];
+    }
+}
+
+// The chunks of each row folded into the first one's place, in chunk order, and the row's loss: one
+// wave per row, 64 chunks at a time through LDS.
+__global__ __launch_bounds__(kWave) void loss_fold_kernel(LossParams p, float *stats, int nch) {
+    __shared__ float s_st[kWave * kStat];
+    const int b = blockIdx.x, lane = threadIdx.x;
+    const bool pair = b < p.P;
+    float *st = stats + (size_t)b * nch * kStat;
+    float ma = -INFINITY, ms = -INFINITY, za = 0.f, zs = 0.f, cross = 0.f;
+    for (int pass = 0; pass < 2; ++pass)
+        for (int q0 = 0; q0 < nch; q0 += kWave) {
+            const int n = min(kWave, nch - q0);
+            for (int i = lane; i < n * kStat; i += kWave) s_st[i] = st[(size_t)q0 * kStat + i];
+            __syncthreads();
+            if (pass == 0)
+                fold_max(s_st, n, pair, ma, ms);
+            else
+                fold_sum(s_st, n, pair, ma, ms, za, zs, cross);
+            __syncthreads();
+        }
+    if (lane == 0) {
+        write_loss(p, b, ma, ms, za, zs, cross);
+        st[0] = ma, st[1] = za, st[3] = ms, st[4] = zs;
+    }
+}
+
 // Phase 2, bf16: the logit gradients as MFMA operands, without an fp32 copy in memory. Workgroup
 // (512 vocabulary entries, rows 8 y .. 8 y + 7), one wave: the rows' statistics combined in chunk
 // order (staged through LDS), then each thread forms the gradients of 8 vocabulary entries x 8 rows
@@ -211,7 +267,13 @@ __global__ __launch_bounds__(256) void pack_inputs_kernel(const float *T0, const
 // of ldz x rpad, rows rows .. rpad - 1 zero). Latency bounds it: every logit load is issued before
 // the first is used. At the 7B head
 // (64 rows) 22 us in the place of 10 (fp32 gradients) + 12 (their packing).
-constexpr int kGradThreads = kWave;
+//
+// FOLDED: the statistics of a row are already one chunk (loss_fold_kernel). A vocabulary of more than
+// kStageChunks chunks takes it: the stage of eight rows is 160 bytes a chunk and every workgroup
+// repeats the fold, so from there on (20 KiB, eight workgroups per CU) the stage limits the waves on
+// a CU, and above a million entries it would not fit the LDS.
+constexpr int kGradThreads = kWave, kStageChunks = 128;
+template <bool FOLDED>
 __global__ __launch_bounds__(kGradThreads) void loss_grad_pack_kernel(LossParams p, const float *stats, int nch, int cap,
                                                                       uint16_t *Dact, int rpad, uint16_t *DT) {
     struct Row {
@@ -222,42 +284,32 @@ __global__ __launch_bounds__(kGradThreads) void loss_grad_pack_kernel(LossParams
     __shared__ Row s_row[8];
     extern __shared__ float s_stat[];  // the statistics of the eight rows [8][nch][kStat]
     const int c = blockIdx.x, r0 = blockIdx.y * 8, tid = threadIdx.x, V = p.V, rows = p.P + p.A;
-    for (int i = tid; i < min(8, rows - r0) * nch * kStat; i += kGradThreads) s_stat[i] = stats[(size_t)r0 * nch * kStat + i];
-    __syncthreads();
+    if constexpr (!FOLDED) {
+        for (int i = tid; i < min(8, rows - r0) * nch * kStat; i += kGradThreads)
+            s_stat[i] = stats[(size_t)r0 * nch * kStat + i];
+        __syncthreads();
+    }
     if (tid < 8) {
         Row q{p.Z, p.Z, 0.f, 0.f, 0.f, 0.f, 0, 0};  // no row: loads row 0, uses none of it
         const int b = r0 + tid;
-        const float *st = s_stat + tid * nch * kStat;
-        if (b < p.P) {
-            float ma = -INFINITY, ms = -INFINITY;
-            for (int k = 0; k < nch; ++k) {
-                ma = fmaxf(ma, st[k * kStat + 0]);
-                ms = fmaxf(ms, st[k * kStat + 3]);
-            }
-            float za = 0.f, zs = 0.f, cross = 0.f;
-            for (int k = 0; k < nch; ++k) {
-                const float fa = expf(st[k * kStat + 0] - ma);
-                za += st[k * kStat + 1] * fa;
-                cross += st[k * kStat + 2] * fa;
-                zs += st[k * kStat + 4] * expf(st[k * kStat + 3] - ms);
-            }
-            // KL(p || q) = sum_v p_v (a_v - s_v) - logsumexp(a) + logsumexp(s)
-            if (c == 0) p.kl[b] = cross / za - (ma + logf(za)) + (ms + logf(zs));
-            q = Row{p.Z + (size_t)b * p.ldz, p.Z + (size_t)(p.P + b) * p.ldz, ma, 1.0f / za, ms, 1.0f / zs, 0, 1};
-        } else if (b < rows) {
-            const int i = b - p.P, t = p.targets[i];
-            const float *z = p.Z + (size_t)(2 * p.P + i) * p.ldz;
-            q = Row{z, z, 0.f, 0.f, 0.f, 0.f, t, t < 0 || t >= V ? 3 : 2};
-            if (q.kind == 3) {  // a target outside the vocabulary: NaN loss and gradient row
-                if (c == 0) p.nll[i] = NAN;
+        if (b < rows) {
+            const bool pair = b < p.P;
+            float ma = -INFINITY, ms = -INFINITY, za = 0.f, zs = 0.f, cross = 0.f;
+            if constexpr (FOLDED) {
+                const float *st = stats + (size_t)b * nch * kStat;  // where loss_fold_kernel left them
+                ma = st[0], za = st[1], ms = st[3], zs = st[4];
             } else {
-                float mc = -INFINITY;
-                for (int k = 0; k < nch; ++k) mc = fmaxf(mc, st[k * kStat + 0]);
-                float zc = 0.f;
-                for (int k = 0; k < nch; ++k) zc += st[k * kStat + 1] * expf(st[k * kStat + 0] - mc);
-                if (c == 0) p.nll[i] = mc + logf(zc) - z[t];
-                q.ma = mc;
-                q.ia = 1.0f / zc;
+                const float *st = s_stat + tid * nch * kStat;
+                fold_max(st, nch, pair, ma, ms);
+                fold_sum(st, nch, pair, ma, ms, za, zs, cross);
+                if (c == 0) write_loss(p, b, ma, ms, za, zs, cross);
+            }
+            if (pair) {
+                q = Row{p.Z + (size_t)b * p.ldz, p.Z + (size_t)(p.P + b) * p.ldz, ma, 1.0f / za, ms, 1.0f / zs, 0, 1};
+            } else {
+                const int i = b - p.P, t = p.targets[i];
+                const float *z = p.Z + (size_t)(2 * p.P + i) * p.ldz;
+                q = Row{z, z, ma, 1.0f / za, 0.f, 0.f, t, t < 0 || t >= V ? 3 : 2};
             }
         }
         s_row[tid] = q;
@@ -516,15 +568,20 @@ hipError_t launch_loss_grad_f32(const LossParams &p, const float *stats, int cap
     return hipGetLastError();
 }
 
-hipError_t launch_loss_grad_pack(const LossParams &p, const float *stats, int cap, uint16_t *Dact, int rpad, uint16_t *DT,
+hipError_t launch_loss_grad_pack(const LossParams &p, float *stats, int cap, uint16_t *Dact, int rpad, uint16_t *DT,
                                  hipStream_t s, hipEvent_t e1) {
     const int rows = p.P + p.A;
     if (!loss_params_ok(p) || rows > cap || p.ldz % 64 != 0 || rpad % 32 != 0 || rpad < rows) return hipErrorInvalidValue;
     const int nch = (p.ldz + kLossChunk - 1) / kLossChunk;
-    const size_t lds = (size_t)8 * nch * kStat * sizeof(float);
-    if (lds > 96 * 1024) return hipErrorInvalidValue;  // a vocabulary of more than a million entries
-    hipExtLaunchKernelGGL(loss_grad_pack_kernel, dim3((p.ldz / 8 + kGradThreads - 1) / kGradThreads, rpad / 8), dim3(kGradThreads), lds, s, nullptr, e1, 0, p, stats,
-                          nch, cap, Dact, rpad, DT);
+    const dim3 grid((p.ldz / 8 + kGradThreads - 1) / kGradThreads, rpad / 8), block(kGradThreads);
+    if (nch > kStageChunks) {
+        hipLaunchKernelGGL(loss_fold_kernel, dim3(rows), dim3(kWave), 0, s, p, stats, nch);
+        hipExtLaunchKernelGGL(loss_grad_pack_kernel<true>, grid, block, 0, s, nullptr, e1, 0, p, (const float *)stats, nch,
+                              cap, Dact, rpad, DT);
+    } else {
+        hipExtLaunchKernelGGL(loss_grad_pack_kernel<false>, grid, block, (size_t)8 * nch * kStat * sizeof(float), s,
+                              nullptr, e1, 0, p, (const float *)stats, nch, cap, Dact, rpad, DT);
+    }
     return hipGetLastError();
 }
 
