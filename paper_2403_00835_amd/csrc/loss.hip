@@ -457,7 +457,11 @@ __global__ __launch_bounds__(kLossThreads) void hidden_rows_kernel(const float *
 // 145 with ordinary stores; 64 x 256 blocks 110; one workgroup per strip of blocks with its H
 // operand kept in registers 104, but slower in a whole call (298 against 286 us); 16-byte stores
 // straight from the registers (64-byte row pieces) 159.
+//
+// dW is the caller's, of which 4-byte alignment is all that is known: the store type says so, and the
+// hardware takes a 16-byte store at any 4-byte address.
 constexpr int kDwV = 128, kDwK = 128, kDwLd = kDwK + 4;  // LDS row stride (floats)
+typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 __global__ __launch_bounds__(256) void loss_dw_mfma_kernel(const uint16_t *DT, const uint16_t *HT, int Vp, int d,
                                                            int rpad, int V, float *dW) {
     extern __shared__ float s_blk[];  // kDwV x kDwLd
@@ -514,7 +518,7 @@ __global__ __launch_bounds__(256) void loss_dw_mfma_kernel(const uint16_t *DT, c
             const int v = kDwV * blockIdx.y + r;
             if (v < V)
                 __builtin_nontemporal_store(*reinterpret_cast<const f32x4 *>(s_blk + r * kDwLd + c),
-                                            reinterpret_cast<f32x4 *>(dW + (size_t)v * d + k));
+                                            reinterpret_cast<f32x4_a4 *>(dW + (size_t)v * d + k));
         }
     }
 }

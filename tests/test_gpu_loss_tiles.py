@@ -40,3 +40,31 @@ def test_loss_head_tiles(head, P, A):
     _close_array(g["d_student"], o["d_student"], sc_s, tol, "d_student")
     _close_array(g["d_ar"], o["d_ar"], sc_a, tol, "d_ar")
     _close_array(g["d_W"], o["d_W"], sc_w, tol, "d_W")
+
+
+@pytest.mark.parametrize("off", [1, 2, 3])
+def test_loss_head_device_unaligned_arrays(head, off):
+    """Slices of a flat buffer at any float offset: the results of aligned arrays, nothing beside them."""
+    import torch
+    m, _ = head
+    P, A, d, V = 5, 4, CFG.d_model, CFG.vocab
+    t, s, ar, tg = workload.make_head_rows(CFG, P, A, seed=53)
+    h = m.loss_head(t, s, ar, tg, 0.7, want_dw=True)
+
+    def at(values):
+        flat = torch.full((off + values.size + 4,), 7.0, device="cuda")
+        flat[off:off + values.size] = torch.from_numpy(values.ravel()).cuda()
+        return flat, flat[off:off + values.size].view(values.shape)
+
+    ins = [at(x)[1] for x in (t, s, ar)]
+    outs = [at(np.zeros(n, np.float32)) for n in ((P,), (A,), (P, d), (A, d), (V, d))]
+    loss = torch.zeros(1, dtype=torch.float64, device="cuda")
+    TG = torch.from_numpy(tg).cuda()
+    torch.cuda.synchronize()
+    log(f"[loss-tiles] arrays {off} floats past an aligned address")
+    m.loss_head_device(P, A, 0.7, *ins, TG, *(o[1] for o in outs), loss)
+    torch.cuda.synchronize()
+    for (flat, view), key in zip(outs, ("kl", "nll", "d_student", "d_ar", "d_W")):
+        assert np.array_equal(view.cpu().numpy(), h[key]), key
+        assert bool((flat[:off] == 7.0).all()) and bool((flat[off + view.numel():] == 7.0).all()), key
+    assert loss.item() == h["loss"]
