@@ -327,6 +327,7 @@ struct IterShape {
     bool prompt = false;  // prompt rows (a prefill chunk): bf16 products take the prompt GEMM
     uint64_t lm_mask = 0;   // != 0: the LM head runs only on these 64-row tiles (packed prefill)
     uint64_t adv_mask = 0;  // prefill entries whose chunk does not end their prompt
+    int attn_tiles = 0;     // prompt: 64-row tiles of the entries, added up
 };
 
 cllm_status enqueue_iteration(cllm_ctx *c, const IterShape &sh, int32_t *out_dev, const int32_t *stream_dev) {
@@ -410,7 +411,7 @@ cllm_status enqueue_iteration(cllm_ctx *c, const IterShape &sh, int32_t *out_dev
         // head's K from L2), and the chunk-parallel pair for the rest; these two give
         // bit-identical values.
         if (prompt_gemm && c->hd <= 128) {
-            HIPCHK(c, launch_attn_prompt(sh.maxm, sh.nseq, ap, s, e0, e1));
+            HIPCHK(c, launch_attn_prompt(sh.R, sh.maxm, sh.attn_tiles, sh.nseq, sh.nch, ap, s, e0, e1));
         } else if (sh.nseq == 1 && sh.nch <= kFusedChunks && c->hd <= 128 && sh.maxm <= kMaxRows) {
             HIPCHK(c, launch_attn_fused(c->bf16, ceil_div(std::max(sh.maxm, 1), 16), sh.nseq, ap, s, e0, e1));
         } else {
@@ -602,6 +603,7 @@ cllm_status prefill_impl(cllm_ctx *c, int seq, const int32_t *prompt, int len) {
         IterShape sh{rows, 1, rows, std::min(c->nch, ceil_div(start + rows, kAttnChunk)), last,
                      last ? (rows - 1) / kMaxRows : -1};
         sh.prompt = true;
+        sh.attn_tiles = ceil_div(rows, kMaxRows);
         st = enqueue_iteration(c, sh, nullptr, nullptr);
         if (st) return st;
     }
@@ -637,7 +639,7 @@ cllm_status prefill_packed_impl(cllm_ctx *c, int B, const int32_t *seq_ids, cons
         // buffer, valid for the whole call)
         const int32_t *zs = prompts + off[b] + done[b];
         uint64_t reset = 0, adv = 0, lm = 0;
-        int R = 0, maxm = 0, nch = 1;
+        int R = 0, maxm = 0, nch = 1, tiles = 0;
         while (b < B && R < chunk && (int)seq.size() < kMaxSeqs) {
             const int e = (int)seq.size(), take = std::min(lens[b] - done[b], chunk - R);
             seq.push_back(seq_ids[b]);
@@ -646,6 +648,7 @@ cllm_status prefill_packed_impl(cllm_ctx *c, int B, const int32_t *seq_ids, cons
             done[b] += take;
             nch = std::max(nch, ceil_div(done[b], kAttnChunk));
             maxm = std::max(maxm, take);
+            tiles += ceil_div(take, kMaxRows);
             R += take;
             if (done[b] == lens[b]) {
                 lm |= 1ull << ((R - 1) / kMaxRows);
@@ -659,6 +662,7 @@ cllm_status prefill_packed_impl(cllm_ctx *c, int B, const int32_t *seq_ids, cons
         if (st) return st;
         IterShape sh{R, ne, maxm, std::min(c->nch, nch), lm != 0, -1};
         sh.prompt = true;
+        sh.attn_tiles = tiles;
         sh.lm_mask = R > kMaxRows ? lm : 0;
         sh.adv_mask = adv;
         st = enqueue_iteration(c, sh, nullptr, nullptr);

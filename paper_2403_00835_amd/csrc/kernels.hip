@@ -464,21 +464,40 @@ __global__ __launch_bounds__(kWave * RG) void attn_partial_kernel(AttnParams p) 
 }
 
 // ------------------------------------------------------------------------------------------
-// Attention of prompt rows (prefill passes, bf16, head_dim <= 128): one kernel, no partials in
-// memory. Workgroup (head h, 64 rows of a batch entry), 8 waves: 4 row groups of 16 rows x the even
-// and the odd 64-key chunks (at absolute positions). A wave walks its chunks with a running maximum
-// per row (rescaling its sum and output when the maximum grows); the two halves are merged through
-// LDS at the end. Per chunk the arithmetic is attn_partial_kernel's: S^T = K Q^T (query hi and lo
-// planes), base-2 softmax in fp32, O^T += V^T P^T (probabilities hi and lo). The chunks of a
-// pair of steps come into LDS by DMA, once for all waves, one pair ahead. A row's value depends on
-// its position and the cache only, not on the rows or the pass it is computed with.
+// Attention of prompt rows (prefill passes, bf16, head_dim <= 128). Workgroup (head h, 64 rows of a
+// batch entry), 8 waves: 4 row groups of 16 rows x the even and the odd 64-key chunks (at absolute
+// positions). A wave walks its chunks with a running maximum per row (rescaling its sum and output
+// when the maximum grows). The keys are cut into pieces of kPromptPiece pairs of chunks, at
+// absolute positions: each piece starts from an empty state, and its state is merged into the
+// row's in position order; at the end the two halves are merged through LDS. Per chunk the
+// arithmetic is attn_partial_kernel's: S^T = K Q^T (query hi and lo planes), base-2 softmax in fp32,
+// O^T += V^T P^T (probabilities hi and lo). The chunks of a pair of steps come into LDS by DMA, once
+// for all waves, one pair ahead.
+//
+// SPLIT: a workgroup takes one piece, writes its halves' states, and attn_prompt_merge_kernel merges
+// them, through the same functions and in the same order: for launches of so few workgroups that
+// most CUs would idle while each walks a long context. A row's value depends on its position and
+// the cache only, not on the rows, the pass or the split it is computed with.
 //
 // What bounds it: LDS reads (each row group reads the whole chunk) and the softmax's VALU work,
 // about as long as the MFMAs. Against the chunk-parallel pair, which wrote and read the partials
 // (rows x head_dim x 4 B per chunk, as much as the K and V they summarise), 512 rows, 32 heads of
-// 128: 39 -> 19 us at 512 keys, 92 -> 37 us on average over the four passes of 1999 keys.
+// 128: 38 -> 18 us at 512 keys, 100 -> 41 us on average over the four passes of 2048 keys (39 without
+// pieces: their merges cost 3-7% of a long walk).
 // ------------------------------------------------------------------------------------------
 constexpr int kPromptAttnRows = 64;
+constexpr int kPromptPiece = 4;  // pairs of chunks per piece (512 keys)
+
+// Softmax state of one row over some of its keys: maximum M, sum l (and the output, kept apart).
+// Merging (M, l, o) and (Ms, ls, os): the weights of the two, then each value; explicit multiplies
+// and fused adds, so that every kernel rounds alike.
+__device__ __forceinline__ void merge_weights(float &M, float Ms, float &w, float &ws) {
+    const float Mn = fmaxf(M, Ms);
+    w = M == -INFINITY ? 0.0f : exp2f(M - Mn);
+    ws = Ms == -INFINITY ? 0.0f : exp2f(Ms - Mn);
+    M = Mn;
+}
+__device__ __forceinline__ float merge_value(float x, float xs, float w, float ws) { return __builtin_fmaf(xs, ws, x * w); }
 
 template <int HD>
 __host__ __device__ constexpr int prompt_attn_lds_bytes() {
@@ -487,8 +506,8 @@ __host__ __device__ constexpr int prompt_attn_lds_bytes() {
     return stage > merge ? stage : merge;
 }
 
-template <int HD>
-__global__ __launch_bounds__(8 * kWave, 2) void attn_prompt_kernel(AttnParams p) {
+template <int HD, bool SPLIT>
+__global__ __launch_bounds__(8 * kWave, 2) void attn_prompt_kernel(AttnParams p, int npiece) {
     constexpr Prec P = Prec::BF16;
     using PT = PrecT<P>;
     constexpr int NKK = HD / PT::KSTEP, NDT = HD / 16;
@@ -496,7 +515,7 @@ __global__ __launch_bounds__(8 * kWave, 2) void attn_prompt_kernel(AttnParams p)
     constexpr int NLW = 2 * BLK / 8;                              // DMA loads per wave and pair of chunks
     const RowTab *tab = p.rr.tab;
     request_together(tab, p.Q, p.Kc, p.Vt, p.kv_seq, p.ctx_alloc, p.rr.cap, p.d, p.O);
-    const int h = blockIdx.x, b = blockIdx.z;
+    const int h = blockIdx.x, b = SPLIT ? blockIdx.z / npiece : blockIdx.z, piece = SPLIT ? blockIdx.z % npiece : 0;
     const int rbase = (int)(gridDim.y - 1 - blockIdx.y) * kPromptAttnRows;  // the longest rows first
     const int nseq = tab->nseq, m = tab->m[b], L = tab->L[b], r0 = tab->r0[b], slot = tab->seq[b];
     request_together(nseq, m, L, r0, slot);
@@ -510,6 +529,8 @@ __global__ __launch_bounds__(8 * kWave, 2) void attn_prompt_kernel(AttnParams p)
     const int qld = min(r0 + qi, p.rr.cap - 1);  // rows past the entry load in-bounds filler
     const int qpos = L + qi;
     const int npair = ((L + min(m - 1, rbase + kPromptAttnRows - 1)) / kAttnChunk + 2) / 2;  // pairs of chunks with a visible key
+    const int it0 = piece * kPromptPiece, it1 = SPLIT ? min(npair, it0 + kPromptPiece) : npair;
+    if (SPLIT && it0 >= npair) return;  // no row sees the piece
     const int wlast = L + min(m - 1, rbase + 16 * rg + 15);  // the wave's last position
     const bool live = rbase + 16 * rg < m;                   // uniform over the wave
     const size_t kvo = (size_t)slot * p.kv_seq + (size_t)h * p.ctx_alloc * HD;
@@ -541,18 +562,17 @@ __global__ __launch_bounds__(8 * kWave, 2) void attn_prompt_kernel(AttnParams p)
         for (int pl = 0; pl < 2; ++pl)
             qv[pl][kk] = *reinterpret_cast<const u32x4 *>(
                 Q + pl * act_plane(p.rr.cap, d) + act_idx<P>(qld, h * HD + kk * PT::KSTEP + g * PT::VEC, d));
-    issue(0, 0);
+    issue(it0, 0);  // it0 is even: a pair's buffer is its index's parity
 
-    float M = -INFINITY, l = 0.0f;
+    float M = -INFINITY, l = 0.0f;  // the piece's state
     f32x4 o[NDT];
+    float Mr = -INFINITY, lr = 0.0f;  // the row's, over the pieces before
+    f32x4 orow[NDT];
 #pragma unroll
-    for (int dt = 0; dt < NDT; ++dt) o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int it = 0; it < npair; ++it) {
-        wait_vm_lds<0>();    // this wave's blocks of the pair have landed, its reads of the other buffer are done
-        barrier_no_fence();  // every wave's
-        if (it + 1 < npair) issue(it + 1, (it + 1) & 1);
+    for (int dt = 0; dt < NDT; ++dt) o[dt] = orow[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto chunk = [&](int it) {
         const int key0 = (2 * it + half) * kAttnChunk;
-        if (!live || key0 > wlast) continue;  // no row of the wave sees the chunk
+        if (!live || key0 > wlast) return;  // no row of the wave sees the chunk
         const u32x4 *kv = s_kv + (size_t)((it & 1) * 2 + half) * BLK * kWave + lane;
         f32x4 st[4];
 #pragma unroll
@@ -622,9 +642,49 @@ __global__ __launch_bounds__(8 * kWave, 2) void attn_prompt_kernel(AttnParams p)
                 o[dt] = mfma_kstep<P>(vb, ph[kp], o[dt]);
                 o[dt] = mfma_kstep<P>(vb, plo[kp], o[dt]);
             }
+    };
+    for (int it = it0; it < it1; ++it) {
+        wait_vm_lds<0>();    // this wave's blocks of the pair have landed, its reads of the other buffer are done
+        barrier_no_fence();  // every wave's
+        if (it + 1 < it1) issue(it + 1, (it + 1) & 1);
+        chunk(it);
+        if (it + 1 < it1 && (it + 1) % kPromptPiece != 0) continue;
+        // the piece's end
+        l += __shfl_xor(l, 16);
+        l += __shfl_xor(l, 32);
+        if (SPLIT || it < kPromptPiece) {  // the first one
+            Mr = M;
+            lr = l;
+#pragma unroll
+            for (int dt = 0; dt < NDT; ++dt) orow[dt] = o[dt];
+        } else {
+            float w0, w1;
+            merge_weights(Mr, M, w0, w1);
+            lr = merge_value(lr, l, w0, w1);
+#pragma unroll
+            for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) orow[dt][v] = merge_value(orow[dt][v], o[dt][v], w0, w1);
+        }
+        if (!SPLIT) {
+            M = -INFINITY;
+            l = 0.0f;
+#pragma unroll
+            for (int dt = 0; dt < NDT; ++dt) o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
     }
-    l += __shfl_xor(l, 16);
-    l += __shfl_xor(l, 32);
+    if constexpr (SPLIT) {
+        if (qi < m) {
+            const size_t sb = ((size_t)h * p.nch + 2 * piece + half) * p.rr.cap + r0 + qi;
+#pragma unroll
+            for (int dt = 0; dt < NDT; ++dt) *reinterpret_cast<f32x4 *>(p.Opart + sb * HD + 16 * dt + 4 * g) = orow[dt];
+            if (g == 0) {
+                p.Mpart[sb] = Mr;
+                p.Lpart[sb] = lr;
+            }
+        }
+        return;
+    }
     // merge: the odd half's state through LDS, lane by lane (the same row and dims)
     wait_vm_lds<0>();
     __syncthreads();
@@ -633,16 +693,15 @@ __global__ __launch_bounds__(8 * kWave, 2) void attn_prompt_kernel(AttnParams p)
 #pragma unroll
         for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) s_m[(4 * dt + v) * kWave] = o[dt][v];
-        s_m[(HD / 4) * kWave] = M;
-        s_m[(HD / 4 + 1) * kWave] = l;
+            for (int v = 0; v < 4; ++v) s_m[(4 * dt + v) * kWave] = orow[dt][v];
+        s_m[(HD / 4) * kWave] = Mr;
+        s_m[(HD / 4 + 1) * kWave] = lr;
     }
     __syncthreads();
     if (half == 1 || qi >= m) return;
-    const float M1 = s_m[(HD / 4) * kWave], l1 = s_m[(HD / 4 + 1) * kWave];
-    const float Mt = fmaxf(M, M1);  // chunk 0 holds a visible key of every row: finite
-    const float w0 = M == -INFINITY ? 0.0f : exp2f(M - Mt), w1 = M1 == -INFINITY ? 0.0f : exp2f(M1 - Mt);
-    const float den = w0 * l + w1 * l1;
+    float w0, w1;
+    merge_weights(Mr, s_m[(HD / 4) * kWave], w0, w1);
+    const float den = merge_value(lr, s_m[(HD / 4 + 1) * kWave], w0, w1);
     uint16_t *O = reinterpret_cast<uint16_t *>(p.O);
     const size_t plane = act_plane(p.rr.cap, d);
 #pragma unroll
@@ -650,7 +709,7 @@ __global__ __launch_bounds__(8 * kWave, 2) void attn_prompt_kernel(AttnParams p)
         alignas(8) uint16_t hi[4], lo[4];
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            const float x = (w0 * o[dt][v] + w1 * s_m[(4 * dt + v) * kWave]) / den;
+            const float x = merge_value(orow[dt][v], s_m[(4 * dt + v) * kWave], w0, w1) / den;
             hi[v] = f2bf(x);
             lo[v] = f2bf(x - bf2f(hi[v]));
         }
@@ -658,6 +717,56 @@ __global__ __launch_bounds__(8 * kWave, 2) void attn_prompt_kernel(AttnParams p)
         *reinterpret_cast<u32x2 *>(O + i) = *reinterpret_cast<const u32x2 *>(hi);
         *reinterpret_cast<u32x2 *>(O + plane + i) = *reinterpret_cast<const u32x2 *>(lo);
     }
+}
+
+// The merge of a split prompt launch: one workgroup per (head, row), one thread per output dim. The
+// states of the row's pieces, each half's in position order, then the two halves, as
+// attn_prompt_kernel merges them.
+__global__ __launch_bounds__(128) void attn_prompt_merge_kernel(AttnParams p) {
+    constexpr Prec P = Prec::BF16;
+    constexpr int U = 4;  // pieces whose values are in flight
+    const int h = blockIdx.x, row = blockIdx.y, dim = threadIdx.x;  // row < row capacity (launcher)
+    request_together(p.rr.tab, p.rr.rows, p.rr.cap, p.Mpart, p.Lpart, p.Opart, p.nch, p.hd);
+    const int R = p.rr.tab->R;
+    const int pos = p.rr.rows[row].pos;
+    request_together(R, pos);
+    if (row >= R || dim >= p.hd) return;
+    const int n = pos / (2 * kPromptPiece * kAttnChunk) + 1;  // pieces with a key that the row sees
+    const size_t b0 = (size_t)h * p.nch * p.rr.cap + row;
+    float M[2], l[2], o[2];
+    for (int q0 = 0; q0 < n; q0 += U) {
+        float Ms[U][2], ls[U][2], os[U][2];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const size_t sb = b0 + (size_t)(2 * min(q0 + u, n - 1) + e) * p.rr.cap;
+                Ms[u][e] = p.Mpart[sb];
+                ls[u][e] = p.Lpart[sb];
+                os[u][e] = p.Opart[sb * p.hd + dim];
+            }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (q0 + u >= n) break;
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                if (q0 + u == 0) {
+                    M[e] = Ms[u][e];
+                    l[e] = ls[u][e];
+                    o[e] = os[u][e];
+                } else {
+                    float w0, w1;
+                    merge_weights(M[e], Ms[u][e], w0, w1);
+                    l[e] = merge_value(l[e], ls[u][e], w0, w1);
+                    o[e] = merge_value(o[e], os[u][e], w0, w1);
+                }
+            }
+        }
+    }
+    float w0, w1;
+    merge_weights(M[0], M[1], w0, w1);
+    const float x = merge_value(o[0], o[1], w0, w1) / merge_value(l[0], l[1], w0, w1);
+    put_act<P>(reinterpret_cast<uint16_t *>(p.O), act_plane(p.rr.cap, p.d), act_idx<P>(row, h * p.hd + dim, p.d), x);
 }
 
 // Combine the chunk partials of one (head, row) in chunk order and write the O operand.
@@ -1058,22 +1167,51 @@ hipError_t launch_embed(bool bf16, int rows, const EmbedParams &p, hipStream_t s
     return hipGetLastError();
 }
 
-hipError_t launch_attn_prompt(int max_rows, int nseq, const AttnParams &p, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-    if (max_rows < 1 || nseq < 1 || nseq > kMaxSeqs || p.ctx_alloc % kAttnChunk != 0) return hipErrorInvalidValue;
-    const dim3 grid(p.n_heads, (max_rows + kPromptAttnRows - 1) / kPromptAttnRows, nseq), block(8 * kWave);
+hipError_t launch_attn_prompt(int rows, int max_rows, int tiles, int nseq, int nch, const AttnParams &p, hipStream_t s,
+                              hipEvent_t e0, hipEvent_t e1) {
+    if (rows < 1 || rows > p.rr.cap || max_rows < 1 || tiles < 1 || nseq < 1 || nseq > kMaxSeqs || nch < 1 || nch > p.nch ||
+        p.ctx_alloc % kAttnChunk != 0)
+        return hipErrorInvalidValue;
+    // Pieces side by side where fewer than half the CUs have a workgroup and the walk is longer than
+    // a piece and the merge. Measured for 32 heads of 128, us (walk -> pieces; the chunk-parallel
+    // pair): 64 rows behind 512 keys 19 -> 23 (22), 1024: 31 -> 24 (30), 2048: 53 -> 26 (29), 8192:
+    // 190 -> 61 (89); 192 rows behind 1024: 34 -> 28 (36), 8192: 197 -> 137 (254); 256 rows (half the
+    // CUs) behind 1024: 36 -> 39 (46), 8192: 196 -> 189 (339). Pieces of two pairs: 64 rows behind 8192
+    // keys 88, 512 rows 227 (four pairs 214, no pieces 209, the pair 655). One row behind 2048 keys: 51
+    // -> 22 (17): the pair stays ahead there by its shorter launches, not worth another order of sums.
+    const int npiece = (nch + 2 * kPromptPiece - 1) / (2 * kPromptPiece);
+    const bool split = nch > 3 * kPromptPiece && 2 * p.n_heads * tiles < kCUs;
+    const dim3 grid(p.n_heads, (max_rows + kPromptAttnRows - 1) / kPromptAttnRows, split ? nseq * npiece : nseq);
     auto launch = [&](auto kern, int lds) {
-        if (e0)
-            hipExtLaunchKernelGGL(kern, grid, block, lds, s, e0, e1, 0, p);
+        hipEvent_t end = split ? nullptr : e1;
+        if (e0 || end)
+            hipExtLaunchKernelGGL(kern, grid, dim3(8 * kWave), lds, s, e0, end, 0, p, npiece);
         else
-            hipLaunchKernelGGL(kern, grid, block, lds, s, p);
+            hipLaunchKernelGGL(kern, grid, dim3(8 * kWave), lds, s, p, npiece);
         return hipGetLastError();
     };
+    hipError_t err = hipErrorInvalidValue;
     switch (p.hd) {
-    case 32: return launch(attn_prompt_kernel<32>, prompt_attn_lds_bytes<32>());
-    case 64: return launch(attn_prompt_kernel<64>, prompt_attn_lds_bytes<64>());
-    case 128: return launch(attn_prompt_kernel<128>, prompt_attn_lds_bytes<128>());
-    default: return hipErrorInvalidValue;
+    case 32:
+        err = split ? launch(attn_prompt_kernel<32, true>, prompt_attn_lds_bytes<32>())
+                    : launch(attn_prompt_kernel<32, false>, prompt_attn_lds_bytes<32>());
+        break;
+    case 64:
+        err = split ? launch(attn_prompt_kernel<64, true>, prompt_attn_lds_bytes<64>())
+                    : launch(attn_prompt_kernel<64, false>, prompt_attn_lds_bytes<64>());
+        break;
+    case 128:
+        err = split ? launch(attn_prompt_kernel<128, true>, prompt_attn_lds_bytes<128>())
+                    : launch(attn_prompt_kernel<128, false>, prompt_attn_lds_bytes<128>());
+        break;
     }
+    if (err != hipSuccess || !split) return err;
+    const dim3 mgrid(p.n_heads, rows), mblock(p.hd <= 64 ? 64 : 128);
+    if (e1)
+        hipExtLaunchKernelGGL(attn_prompt_merge_kernel, mgrid, mblock, 0, s, nullptr, e1, 0, p);
+    else
+        hipLaunchKernelGGL(attn_prompt_merge_kernel, mgrid, mblock, 0, s, p);
+    return hipGetLastError();
 }
 
 template <Prec P, int HD>

@@ -86,8 +86,11 @@ hipError_t launch_attn_combine(bool bf16, int rows, const AttnParams &p, hipStre
 constexpr int kFusedChunks = 32;
 hipError_t launch_attn_fused(bool bf16, int nrg, int nseq_launch, const AttnParams &p, hipStream_t s, hipEvent_t e0,
                              hipEvent_t e1);
-// Attention of prompt rows (bf16, head_dim 32, 64 or 128): nseq entries of at most max_rows rows.
-hipError_t launch_attn_prompt(int max_rows, int nseq, const AttnParams &p, hipStream_t s, hipEvent_t e0, hipEvent_t e1);
+// Attention of prompt rows (bf16, head_dim 32, 64 or 128): `rows` rows in nseq entries of at most
+// max_rows, in `tiles` tiles of 64 rows of an entry, with no row beyond the first nch chunks. Long
+// contexts behind few tiles run in pieces, through the partials' buffers, to the same bits.
+hipError_t launch_attn_prompt(int rows, int max_rows, int tiles, int nseq, int nch, const AttnParams &p, hipStream_t s,
+                              hipEvent_t e0, hipEvent_t e1);
 hipError_t launch_scan(int nseq_launch, const ScanParams &p, hipStream_t s, hipEvent_t e0, hipEvent_t e1);
 hipError_t launch_decode_init(int nseq, const ScanParams &p, hipStream_t s);
 hipError_t launch_plan(const PlanParams &p, hipStream_t s);

@@ -46,3 +46,27 @@ def test_prompt_tiles_against_oracle(shape):
             else:
                 assert np.array_equal(lg, got[n]), f"{n} rows: 64-row passes differ"
         gpu.close()
+
+
+@pytest.mark.parametrize("shape", list(SHAPES))
+def test_prompt_passes_above_512_rows(shape):
+    """Passes of up to 1100 rows (more than one round of the largest tile) give the bits of 64-row passes,
+    which the oracle pins above."""
+    from paper_2403_00835_amd import binding
+    cfg = SHAPES[shape]
+    ws = workload.make_weights(cfg, seed=31)
+    prompt = workload.make_prompt(cfg, 1100, seed=33)
+    block = workload.make_prompt(cfg, 8, seed=34)
+    got = {}
+    for chunk in (64, 2048):
+        gpu = binding.Model(cfg, max_ctx=1200, max_block=8, max_new=8, weights=ws, prefill_chunk=chunk)
+        gpu.debug_logits(True)
+        for n in (513, 640, 897, 1024, 1025, 1100):
+            log(f"[prompt-tiles] {shape}: prefill of {n} rows, chunk {chunk}")
+            block[0] = gpu.prefill(prompt[:n])
+            res = (gpu.last_logits((n - 1) % 64 + 1), gpu.hidden_rows(block))
+            if chunk == 64:
+                got[n] = res
+            else:
+                assert all(np.array_equal(a, b) for a, b in zip(res, got[n])), f"{n} rows: one pass differs"
+        gpu.close()
