@@ -1389,56 +1389,82 @@ static hipError_t launch_prompt_t(const GemmParams &p, int rows, hipStream_t s, 
     return launch_prompt_reduce(p, nsplit, q.zstride, rows, s, e1);
 }
 
-// Workgroups of a prompt product in 16 RG x 16 NT tiles over `splits` K ranges.
-template <int NT, int RG>
-static bool prompt_fits(const GemmParams &p, int rows, int splits) {
-    return (p.cols + 16 * NT - 1) / (16 * NT) * ((rows + 16 * RG - 1) / (16 * RG)) * splits <= kCUs;
+// Tile rule of the prompt products: the tile whose launch should take the least time, a + b rounds.
+// A round is one workgroup per CU (32 on an XCD, which holds the column groups cg with cg % 8 its
+// number: 20 groups are three on four of the XCDs and two on the others); b is the time of a
+// round and a what the first one adds (ramp; the smaller tiles, two of which share a CU, hide part
+// of the later ones' latency). A second, partly filled round costs as much as a full one, and a
+// larger tile than needed leaves CUs idle while its workgroups take longer. The constants are us at
+// 128 k-steps, fitted to forced-tile sweeps over d 2048, 3072, 4096 and 5120 and 64 to 2048 rows;
+// time is nearly proportional to the k-steps for every tile, so the choice does not depend on them.
+// A row's values do not depend on the tile. Of the sweep's 208 launches the rule takes the fastest tile,
+// or one within 2%, but for five (at most 6% off). Against the former rule (the smallest tile whose
+// workgroups are one round, else the largest), us a launch: d 5120, 512 rows gate/up 313 -> 273, down
+// 156 -> 141; 192 rows gate/up 148 -> 121; 320 rows down 137 -> 97; d 4096, 640 rows gate/up 253 ->
+// 220; d 3072, 640 rows down 94 -> 66. At the 7B widths up to 512 rows the two choose alike.
+struct PromptTile {
+    int nt, rg;  // 16 nt columns x 16 rg rows
+    float a, b;
+};
+template <size_t N>
+static int prompt_tile(const PromptTile (&tiles)[N], const GemmParams &p, int rows, int splits) {
+    int best = 0;
+    float least = 0.0f;
+    for (int i = 0; i < (int)N; ++i) {
+        const PromptTile &t = tiles[i];
+        const int groups = (p.cols + 16 * t.nt - 1) / (16 * t.nt), row_tiles = (rows + 16 * t.rg - 1) / (16 * t.rg);
+        const int per_xcd = (groups + 7) / 8 * row_tiles * splits;
+        const float cost = t.a + t.b * (float)((per_xcd + kCUs / 8 - 1) / (kCUs / 8));
+        if (i == 0 || cost < least) least = cost, best = i;
+    }
+    return best;
 }
 
 constexpr int kPromptSplitsO = 2, kPromptSplitsDown = 4;
 
 template <int NS>
 static hipError_t launch_prompt_resid(const GemmParams &p, int rows, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-    if (prompt_fits<4, 4>(p, rows, NS)) return launch_prompt_t<4, 4, 2, E_LOGITS, 5, NS>(p, rows, s, e0, e1);
-    if (prompt_fits<8, 4>(p, rows, NS)) return launch_prompt_t<8, 4, 2, E_LOGITS, 5, NS>(p, rows, s, e0, e1);
-    if (prompt_fits<8, 8>(p, rows, NS)) return launch_prompt_t<8, 8, 2, E_LOGITS, 5, NS>(p, rows, s, e0, e1);
-    return launch_prompt_t<16, 8, 2, E_LOGITS, 4, NS>(p, rows, s, e0, e1);
+    static const PromptTile tiles[] = {{4, 4, 8.0f, 16.7f}, {8, 4, 8.5f, 22.0f}, {8, 8, 2.0f, 41.5f}, {16, 8, 2.0f, 66.0f}};
+    switch (prompt_tile(tiles, p, rows, NS)) {
+    case 0: return launch_prompt_t<4, 4, 2, E_LOGITS, 5, NS>(p, rows, s, e0, e1);
+    case 1: return launch_prompt_t<8, 4, 2, E_LOGITS, 5, NS>(p, rows, s, e0, e1);
+    case 2: return launch_prompt_t<8, 8, 2, E_LOGITS, 5, NS>(p, rows, s, e0, e1);
+    default: return launch_prompt_t<16, 8, 2, E_LOGITS, 4, NS>(p, rows, s, e0, e1);
+    }
 }
 
-// Tile rule: the smallest tile whose workgroups still fit the chip in one round (one workgroup per
-// CU; they are too large to share one), the largest tile if none does. A second, partly filled
-// round costs as much as a full one, and a larger tile than needed leaves CUs idle while its
-// workgroups take longer. Measured at the LLaMA-2-7B shape, us per launch (O and down with their
-// reduction), the tile taken first, then the next smaller and the next larger one:
-//   gate/up 512 rows: 128x384 160 (128x192 171); 256: 128x192 87 (64x192 102, 128x384 126);
-//           128: 64x192 55 (64x128 76, 128x192 71); 64: 64x128 42 (64x192 52)
-//   QKV     512: 128x192 91 (64x192 108); 256: 64x192 53 (64x96 66, 128x192 79);
-//           128: 64x96 39 (64x64 60, 64x192 50); 64: 64x64 34 (64x96 38)
-//   O       512: 128x128 50 (64x128 50); 256: 64x128 32 (64x64 38, 128x128 41); 64: 64x64 24 (64x128 27)
-//   down    512: 128x256 91 (128x128 105); 256: 128x128 55 (64x128 62, 128x256 72);
-//           128: 64x128 39 (64x64 52, 128x128 49); 64: 64x64 32 (64x128 35)
+static hipError_t launch_prompt_qkv(const GemmParams &p, int rows, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+    static const PromptTile tiles[] = {{4, 4, 10.0f, 23.5f}, {6, 4, 13.0f, 27.0f}, {12, 4, 3.0f, 48.0f}, {12, 8, 0.0f, 78.0f}};
+    switch (prompt_tile(tiles, p, rows, 1)) {
+    case 0: return launch_prompt_t<4, 4, 2, E_QKV, 5>(p, rows, s, e0, e1);
+    case 1: return launch_prompt_t<6, 4, 4, E_QKV, 5>(p, rows, s, e0, e1);
+    case 2: return launch_prompt_t<12, 4, 2, E_QKV, 5>(p, rows, s, e0, e1);
+    default: return launch_prompt_t<12, 8, 2, E_QKV, 5>(p, rows, s, e0, e1);
+    }
+}
+
+static hipError_t launch_prompt_gate_up(const GemmParams &p, int rows, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+    static const PromptTile tiles[] = {{4, 4, 10.0f, 24.5f}, {8, 4, 14.0f, 29.5f}, {12, 4, 8.0f, 45.0f}, {12, 8, 0.0f, 78.0f},
+                                       {24, 8, 0.0f, 126.0f}};
+    switch (prompt_tile(tiles, p, rows, 1)) {
+    case 0: return launch_prompt_t<4, 4, 4, E_SWIGLU, 5>(p, rows, s, e0, e1);
+    case 1: return launch_prompt_t<8, 4, 2, E_SWIGLU, 5>(p, rows, s, e0, e1);
+    case 2: return launch_prompt_t<12, 4, 4, E_SWIGLU, 5>(p, rows, s, e0, e1);
+    case 3: return launch_prompt_t<12, 8, 4, E_SWIGLU, 5>(p, rows, s, e0, e1);
+    default: return launch_prompt_t<24, 8, 2, E_SWIGLU, 4>(p, rows, s, e0, e1);
+    }
+}
+
 // O and down split K into 2 and 4 ranges (fixed: they are part of a row's reduction order), which
 // gives their 4096 columns as many workgroups at 512 rows as the other products have.
 hipError_t launch_gemm_prompt(GemmKind kind, int rows, const GemmParams &p, hipStream_t s, hipEvent_t e0,
                               hipEvent_t e1) {
     switch (kind) {
-    case GEMM_QKV:
-        if (prompt_fits<4, 4>(p, rows, 1)) return launch_prompt_t<4, 4, 2, E_QKV, 5>(p, rows, s, e0, e1);
-        if (prompt_fits<6, 4>(p, rows, 1)) return launch_prompt_t<6, 4, 4, E_QKV, 5>(p, rows, s, e0, e1);
-        if (prompt_fits<12, 4>(p, rows, 1)) return launch_prompt_t<12, 4, 2, E_QKV, 5>(p, rows, s, e0, e1);
-        return launch_prompt_t<12, 8, 2, E_QKV, 5>(p, rows, s, e0, e1);
-    case GEMM_GATE_UP:
-        if (prompt_fits<4, 4>(p, rows, 1)) return launch_prompt_t<4, 4, 4, E_SWIGLU, 5>(p, rows, s, e0, e1);
-        if (prompt_fits<8, 4>(p, rows, 1)) return launch_prompt_t<8, 4, 2, E_SWIGLU, 5>(p, rows, s, e0, e1);
-        if (prompt_fits<12, 4>(p, rows, 1)) return launch_prompt_t<12, 4, 4, E_SWIGLU, 5>(p, rows, s, e0, e1);
-        if (prompt_fits<12, 8>(p, rows, 1)) return launch_prompt_t<12, 8, 4, E_SWIGLU, 5>(p, rows, s, e0, e1);
-        return launch_prompt_t<24, 8, 2, E_SWIGLU, 4>(p, rows, s, e0, e1);
-    case GEMM_O:  // X += O W_o^T
-        return launch_prompt_resid<kPromptSplitsO>(p, rows, s, e0, e1);
-    case GEMM_DOWN:  // X += H W_d^T
-        return launch_prompt_resid<kPromptSplitsDown>(p, rows, s, e0, e1);
-    default:
-        return hipErrorInvalidValue;
+    case GEMM_QKV: return launch_prompt_qkv(p, rows, s, e0, e1);
+    case GEMM_GATE_UP: return launch_prompt_gate_up(p, rows, s, e0, e1);
+    case GEMM_O: return launch_prompt_resid<kPromptSplitsO>(p, rows, s, e0, e1);        // X += O W_o^T
+    case GEMM_DOWN: return launch_prompt_resid<kPromptSplitsDown>(p, rows, s, e0, e1);  // X += H W_d^T
+    default: return hipErrorInvalidValue;
     }
 }
 
