@@ -399,13 +399,15 @@ __global__ __launch_bounds__(W * kWave) void gemm_kernel(GemmParams p) {
 // 1 KiB each) are loaded once per workgroup from global memory straight into LDS (LDS DMA), into a
 // ring of NB buffers.
 //
-// What bounds it: a CU keeps a fixed amount of loads in flight, so it pulls 65-70 GB/s of operand
-// bytes here whatever the ring's depth (4 or 5 buffers the same, 3 too few), and its LDS reads
-// compete with the MFMAs; both fall with larger tiles. Hence one workgroup per CU with the largest
-// tile that still gives every CU one (128 x 384 for gate/up: 160 KiB of LDS, 232 workgroups at
-// 512 rows), not several small ones. Each wave holds two sets of operand registers: while
-// the MFMAs of a k-step run, the next k-step's operands are read from LDS between them, so neither
-// waits for the other, and the barrier of a k-step finds its operands already in registers.
+// What bounds it: no one unit. At 512 rows of the LLaMA-2-7B shape the MFMAs are busy 52-58% of the
+// cycles (O 35%), and a CU pulls 35-45 GB/s of operands, where the former kernel's smaller tiles were
+// held at 65-70. A k-step's LDS reads and MFMAs overlap in part: gate/up moves 152 KiB through LDS
+// (about 1,220 cycles at 128 B) and issues 384 MFMAs (about 1,540 at peak rate), and takes about
+// 2,800 at 2.4 GHz. Larger tiles move fewer bytes per MFMA, through LDS as from memory. Hence one
+// workgroup per CU with a large tile (128 x 384 for gate/up: 160 KiB of LDS, 232 workgroups at 512
+// rows), not several small ones. Each wave holds two sets of operand registers: while the MFMAs of a
+// k-step run, the next k-step's operands are read from LDS between them, and the barrier of a k-step
+// finds its operands already in registers. Four or five ring buffers measure alike, three too few.
 // Measured at the LLaMA-2-7B shape, 512 rows, random operands, against the former kernel (64 x 256
 // and 64 x 128 tiles, two or three workgroups per CU, the operands of a k-step read, waited for
 // and then multiplied): gate/up 179 -> 150 us, QKV 119 -> 91, down (with its reduction) 102 -> 91,
@@ -1644,7 +1646,10 @@ static hipError_t launch_down(const GemmParams &p, int row_tiles, hipStream_t s,
 // us a launch): QKV 6.0 -> 5.0 (tiles of 48 -> 16 columns: 48 -> 144 workgroups), gate/up 7.0 ->
 // 5.2 (96 -> 32: 43 -> 128), down with its reduction 6.2 and a launch gap -> 5.2. Above 64 k-steps
 // the larger tiles and the K ranges stay: the launch is a stream there (d 4096: QKV 256 workgroups
-// with the larger tile already, down 21.5 us in one launch against 19.1 with its reduction).
+// with the larger tile already, down 21.5 us in one launch against 19.1 with its reduction). Between
+// 65 and 128 k-steps it depends on the rows, which the order of a sum must not: an iteration of a
+// model with FFN 2080 to 4096 would gain 4-10% at 1 and 16 rows with the line at 128 and lose 3-7% at
+// 64 (d 1024, FFN 4096: 352 -> 334 us at one row, 504 -> 545 at 64).
 constexpr int kShortKs = 64, kShortDepth = 4;
 
 // The down product of such a K is one launch, without K ranges and their reduction. The rule reads

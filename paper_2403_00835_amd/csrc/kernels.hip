@@ -3,12 +3,13 @@
 // An iteration over a block of m tokens at positions L .. L+m-1 (Section 3.1: one causal forward
 // pass over the n-token block gives all n greedy predictions) is the launch sequence
 //   embed -> per layer [QKV GEMM (+RMSNorm prologue, +RoPE, +provisional KV write)
-//                       -> attention partials -> attention combine
+//                       -> attention (one kernel, or partials and their combination)
 //                       -> O GEMM (+residual) -> gate/up GEMM (+RMSNorm prologue, +SwiGLU)
 //                       -> down GEMM (+residual)]
 //   -> LM-head GEMM (+RMSNorm prologue, +argmax partials) -> scan/commit.
 // A batched iteration runs the blocks of several sequences at once (their rows packed one after
-// another). Every kernel reads the rows, their sequences and positions from the device row
+// another). A prefill pass is the same sequence over prompt rows, in bf16 with the prompt products
+// and attn_prompt_kernel. Every kernel reads the rows, their sequences and positions from the device row
 // table, so the same launch sequence serves every iteration without host round trips.
 //
 // Determinism: every reduction has a fixed order that depends only on the model shape, never on

@@ -3,11 +3,11 @@
 //
 // Inputs are LM-head input rows H (fp32): P teacher rows (conditioned on the fixed point y*,
 // stop-gradient), P student rows (on the trajectory state y at the same positions) and A rows of
-// the target model's generation with their target ids. The logits Z = H W^T come from the
-// streaming GEMM (E_LOGITS epilogue). Per pair the loss is the forward KL D(p || q) between
+// the target model's generation with their target ids. The logits Z = H W^T come from
+// launch_rows_product (bf16) or gemm_kernel (fp32), E_LOGITS epilogue. Per pair the loss is the forward KL D(p || q) between
 // p = softmax(teacher logits) and q = softmax(student logits); per AR row -log softmax at the
 // target; L = sum KL + omega sum NLL. Backward: D = dL/dZ for the student and AR rows
-// (q - p; omega (softmax - onehot)), dH = D W (the streaming GEMM again, over a transposed copy
+// (q - p; omega (softmax - onehot)), dH = D W (the same products, over a transposed copy
 // of the packed LM head, K split across workgroups) and dW = D^T H (teacher rows get no
 // gradient). In bf16 the fp32 operands D and H enter the MFMAs as hi + lo bf16 planes, as the
 // activations of the forward do. Every sum has a fixed order (per-thread strided runs, fixed
@@ -203,19 +203,20 @@ __global__ __launch_bounds__(256) void pack_inputs_kernel(const float *T0, const
     *reinterpret_cast<u32x4 *>(HT + (size_t)d * rpad + o) = l;
 }
 
-// The statistics of n chunks folded in chunk order (pair: student logits and the cross term too).
-__device__ __forceinline__ void fold_max(const float *st, int n, bool pair, float &ma, float &ms) {
+// The statistics of n chunks folded in chunk order (PAIR: student logits and the cross term too).
+template <bool PAIR>
+__device__ __forceinline__ void fold_max(const float *st, int n, float &ma, float &ms) {
     for (int k = 0; k < n; ++k) {
         ma = fmaxf(ma, st[k * kStat + 0]);
-        if (pair) ms = fmaxf(ms, st[k * kStat + 3]);
+        if constexpr (PAIR) ms = fmaxf(ms, st[k * kStat + 3]);
     }
 }
-__device__ __forceinline__ void fold_sum(const float *st, int n, bool pair, float ma, float ms, float &za, float &zs,
-                                         float &cross) {
+template <bool PAIR>
+__device__ __forceinline__ void fold_sum(const float *st, int n, float ma, float ms, float &za, float &zs, float &cross) {
     for (int k = 0; k < n; ++k) {
         const float fa = expf(st[k * kStat + 0] - ma);
         za += st[k * kStat + 1] * fa;
-        if (pair) {
+        if constexpr (PAIR) {
             cross += st[k * kStat + 2] * fa;
             zs += st[k * kStat + 4] * expf(st[k * kStat + 3] - ms);
         }
@@ -248,9 +249,9 @@ __global__ __launch_bounds__(kWave) void loss_fold_kernel(LossParams p, float *s
             for (int i = lane; i < n * kStat; i += kWave) s_st[i] = st[(size_t)q0 * kStat + i];
             __syncthreads();
             if (pass == 0)
-                fold_max(s_st, n, pair, ma, ms);
+                pair ? fold_max<true>(s_st, n, ma, ms) : fold_max<false>(s_st, n, ma, ms);
             else
-                fold_sum(s_st, n, pair, ma, ms, za, zs, cross);
+                pair ? fold_sum<true>(s_st, n, ma, ms, za, zs, cross) : fold_sum<false>(s_st, n, ma, ms, za, zs, cross);
             __syncthreads();
         }
     if (lane == 0) {
@@ -266,7 +267,7 @@ __global__ __launch_bounds__(kWave) void loss_fold_kernel(LossParams p, float *s
 // planes of cap rows x ldz) and the operand of dW = D^T H (contraction over the rows, DT: two planes
 // of ldz x rpad, rows rows .. rpad - 1 zero). Latency bounds it: every logit load is issued before
 // the first is used. At the 7B head
-// (64 rows) 22 us in the place of 10 (fp32 gradients) + 12 (their packing).
+// (64 rows) 20 us in the place of 10 (fp32 gradients) + 12 (their packing) and a launch.
 //
 // FOLDED: the statistics of a row are already one chunk (loss_fold_kernel). A vocabulary of more than
 // kStageChunks chunks takes it: the stage of eight rows is 160 bytes a chunk and every workgroup
@@ -300,8 +301,13 @@ __global__ __launch_bounds__(kGradThreads) void loss_grad_pack_kernel(LossParams
                 ma = st[0], za = st[1], ms = st[3], zs = st[4];
             } else {
                 const float *st = s_stat + tid * nch * kStat;
-                fold_max(st, nch, pair, ma, ms);
-                fold_sum(st, nch, pair, ma, ms, za, zs, cross);
+                if (pair) {
+                    fold_max<true>(st, nch, ma, ms);
+                    fold_sum<true>(st, nch, ma, ms, za, zs, cross);
+                } else {
+                    fold_max<false>(st, nch, ma, ms);
+                    fold_sum<false>(st, nch, ma, ms, za, zs, cross);
+                }
                 if (c == 0) write_loss(p, b, ma, ms, za, zs, cross);
             }
             if (pair) {

@@ -11,6 +11,12 @@ import oracle
 TOL = {"f32": 1e-4, "bf16": 2e-2}
 
 
+def rel_err(x, ref):
+    """2-norm of the difference over the 2-norm of the reference."""
+    ref = np.asarray(ref, dtype=np.float64)
+    return float(np.linalg.norm(np.asarray(x, dtype=np.float64) - ref) / np.linalg.norm(ref))
+
+
 def log(*a):
     print(*a, flush=True)
     sys.stdout.flush()

@@ -99,8 +99,8 @@ def test_7b_full_size_jacobi_equals_ar(gpu):
 
 
 def test_7b_prompt_chunking_leaves_values_unchanged(gpu):
-    # The benchmark's prefill (one 512-row pass of the prompt GEMM and the chunk-parallel
-    # attention) against eight 64-row passes of a second context with bit-identical weights
+    # The benchmark's prefill (one 512-row pass of the prompt products and the prompt attention)
+    # against eight 64-row passes of a second context with bit-identical weights
     # (drawn on the device): the prompt's last logits, a 16-row iteration's logits over the
     # cache it left and a 64-token decode are bit-identical.
     from paper_2403_00835_amd import binding

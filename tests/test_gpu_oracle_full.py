@@ -3,7 +3,7 @@ protocol: the oracle is fed the GPU's blocks and commits, and every iteration's 
 and accepted length are compared).
 
 - LLaMA-2-7B shape, prompt 512, iterations of 16 rows: the headline's own prefill (one 512-row
-  pass of the prompt GEMMs and the chunk-parallel attention) and decode iterations at contexts
+  pass of the prompt products and the prompt attention) and decode iterations at contexts
   of 513..593 keys, where the one-kernel attention gives its waves a second 64-key chunk and
   the rows of one iteration straddle a chunk boundary.
 - A two-layer model of the 7B width (d 4096, 32 x 128 heads, FFN 11008, vocab 32000), prompt

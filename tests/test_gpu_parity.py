@@ -216,7 +216,7 @@ def test_small_teacher_forced_iterations(small):
 
 def test_small_ragged_prompt_vs_oracle(small):
     # 300 prompt rows in one pass of the prompt GEMM: five 64-row tiles, the last one ragged
-    # (44 live rows), and the chunk-parallel attention; then teacher-forced iterations.
+    # (44 live rows), and the prompt attention; then teacher-forced iterations.
     log("[gpu] small bf16 teacher-forced, prompt 300 (ragged prompt tiles), n=16")
     prompt = workload.make_prompt(SMALL, 300, seed=23)
     _teacher_forced(small, prompt, n=16, steps=4)

@@ -5,7 +5,9 @@ with the oracle's forward; a prefill in 64-row passes (rows behind a committed c
 bits, there and in the logits of a step over the caches it left; and the caches of a pass shared by
 several prompts give the rows of a block the same bits as a prefill of its own.
 
-Tolerance: the suite's bf16 one (2e-2); two layers stay an order of magnitude below.
+Tolerance: the suite's bf16 one (2e-2) on every logit, and in the 2-norm about four times the largest
+measured distance (1.1e-4: keys and values near a bf16 boundary). Probabilities or queries that lost
+their lo plane would be 2^-9 = 2e-3 off.
 """
 import numpy as np
 import pytest
@@ -13,10 +15,11 @@ import pytest
 import oracle
 from paper_2403_00835_amd import workload
 from paper_2403_00835_amd.configs import ModelConfig
-from tests.parity import TOL, log
+from tests.parity import TOL, log, rel_err
 
 pytestmark = pytest.mark.gpu
 
+REL = 4.5e-4
 LENGTHS = [1, 15, 17, 63, 64, 65, 127, 128, 129, 191, 193, 257]
 
 
@@ -42,6 +45,7 @@ def test_prompt_attention(hd):
             if chunk == 0:
                 e = float(np.abs(lg - ref[n - rows:n]).max())
                 assert e <= TOL["bf16"], f"{n} rows: max|dlogit| {e:.4g}"
+                assert rel_err(lg, ref[n - rows:n]) <= REL, f"{n} rows: {rel_err(lg, ref[n - rows:n]):.3g}"
                 got[n] = lg
                 step[n] = gpu.last_logits(8)
             else:
@@ -101,6 +105,7 @@ def test_prompt_attention_long_contexts(hd):
             if chunk == 4096:
                 e = float(np.abs(lg - ref[n - rows:n]).max())
                 assert e <= TOL["bf16"], f"{n} keys: max|dlogit| {e:.4g}"
+                assert rel_err(lg, ref[n - rows:n]) <= REL, f"{n} keys: {rel_err(lg, ref[n - rows:n]):.3g}"
                 got[n], rows_got[n] = lg, hr
             else:
                 assert np.array_equal(lg, got[n]), f"{n} keys: passes of {chunk} rows differ"

@@ -4,7 +4,9 @@ the LLaMA-2-7B width and at a narrow width whose column groups are ragged. The l
 last 64-row tile are compared with the oracle's forward over the longest prompt (a causal pass: the
 rows of a prefix are the same), and a prefill in 64-row passes gives the same bits.
 
-Tolerance: the bf16 one (2e-2), as at full depth; one layer stays an order of magnitude below.
+Tolerance: the bf16 one (2e-2) on every logit, and in the 2-norm about four times the largest measured
+distance (2.9e-4 at the 7B width, 2.3e-5 at the narrow one: keys and values near a bf16 boundary). An
+operand that lost its lo plane would be 2^-9 = 2e-3 off.
 """
 import numpy as np
 import pytest
@@ -12,7 +14,7 @@ import pytest
 import oracle
 from paper_2403_00835_amd import workload
 from paper_2403_00835_amd.configs import ModelConfig
-from tests.parity import TOL, log
+from tests.parity import TOL, log, rel_err
 
 pytestmark = pytest.mark.gpu
 
@@ -20,6 +22,7 @@ SHAPES = {
     "7b-width": ModelConfig(n_layers=1, d_model=4096, n_heads=32, head_dim=128, ffn_dim=11008, vocab=512),
     "d192": ModelConfig(n_layers=2, d_model=192, n_heads=3, head_dim=64, ffn_dim=500, vocab=1000),
 }
+REL = {"7b-width": 1.2e-3, "d192": 1e-4}
 LENGTHS = [1, 16, 17, 64, 65, 128, 129, 192, 193, 256, 257, 385, 512, 513]
 
 
@@ -42,6 +45,8 @@ def test_prompt_tiles_against_oracle(shape):
             if chunk == 0:
                 e = float(np.abs(lg - ref[n - rows:n]).max())
                 assert e <= TOL["bf16"], f"{n} rows: max|dlogit| {e:.4g}"
+                r = rel_err(lg, ref[n - rows:n])
+                assert r <= REL[shape], f"{n} rows: {r:.3g} of the logits' norm"
                 got[n] = lg
             else:
                 assert np.array_equal(lg, got[n]), f"{n} rows: 64-row passes differ"

@@ -5,7 +5,9 @@ eight waves' first k-steps, in bf16 and fp32. Blocks of 1 to 64 rows take every 
 
 The logits of each step are compared with the oracle's forward over prompt and block, and a
 batched step (more than 64 rows: the multi-tile products) gives the bits of the single steps.
-Tolerance: the suite's (1e-4 fp32, 2e-2 bf16); one or two layers stay an order of magnitude below.
+Tolerance: the suite's (1e-4 fp32, 2e-2 bf16) on every logit, and in the 2-norm about four times the
+largest measured distance (fp32 2.5e-7; bf16 5.4e-5, from keys and values near a bf16 boundary). An
+operand that lost its lo plane would be 2^-9 = 2e-3 off.
 """
 import numpy as np
 import pytest
@@ -13,7 +15,7 @@ import pytest
 import oracle
 from paper_2403_00835_amd import workload
 from paper_2403_00835_amd.configs import ModelConfig
-from tests.parity import TOL, log
+from tests.parity import TOL, log, rel_err
 
 pytestmark = pytest.mark.gpu
 
@@ -28,6 +30,7 @@ SHAPES = {
     "f32-k65": ModelConfig(n_layers=1, d_model=128, n_heads=4, head_dim=32, ffn_dim=1030, vocab=300, dtype="f32"),
 }
 BLOCKS = [1, 16, 17, 33, 64]
+REL = {"f32": 1e-6, "bf16": 2.5e-4}
 
 
 @pytest.mark.parametrize("shape", list(SHAPES))
@@ -52,6 +55,7 @@ def test_short_k_products(shape):
         ref = orc.forward_full(np.concatenate([prompt, block]).astype(np.int32))[len(prompt):]
         e = float(np.abs(lg - ref).max())
         assert e <= TOL[cfg.dtype], f"block of {m}: max|dlogit| {e:.4g}"
+        assert rel_err(lg, ref) <= REL[cfg.dtype], f"block of {m}: {rel_err(lg, ref):.3g} of the logits' norm"
         blocks.append(block)
         rows.append(lg)
     log(f"[short-k] {shape}: batched step of {sum(BLOCKS)} rows")
