@@ -325,7 +325,8 @@ cllm_status cllm_loss_head(cllm_ctx *ctx, const float *teacher, const float *stu
  * the same arguments, computation and results (bit for bit), but every array (rows, targets,
  * row_kl, row_nll, d_student, d_ar, d_weight, and loss, a device double) is memory the context's
  * GPU can access: its device memory, managed or pinned host memory; each is checked and anything
- * else is ERR_ARG. The work is enqueued on the context's stream and the call returns without
+ * else is ERR_ARG. An array needs its elements' alignment only (a slice at any float offset). The
+ * work is enqueued on the context's stream and the call returns without
  * waiting: results are ready when that stream reaches this point; the caller keeps the inputs
  * alive and unmodified until then. loss may be NULL (no total). Sizes are not checked beyond the
  * row counts: each array must hold its rows. A target outside [0, V) cannot be checked on the

@@ -399,11 +399,12 @@ __global__ __launch_bounds__(W * kWave) void gemm_kernel(GemmParams p) {
 // 1 KiB each) are loaded once per workgroup from global memory straight into LDS (LDS DMA), into a
 // ring of NB buffers.
 //
-// What bounds it: no one unit. At 512 rows of the LLaMA-2-7B shape the MFMAs are busy 52-58% of the
-// cycles (O 35%), and a CU pulls 35-45 GB/s of operands, where the former kernel's smaller tiles were
-// held at 65-70. A k-step's LDS reads and MFMAs overlap in part: gate/up moves 152 KiB through LDS
-// (about 1,220 cycles at 128 B) and issues 384 MFMAs (about 1,540 at peak rate), and takes about
-// 2,800 at 2.4 GHz. Larger tiles move fewer bytes per MFMA, through LDS as from memory. Hence one
+// What bounds it: the MFMAs and the clock. With random operands, 512 rows of the LLaMA-2-7B shape,
+// gate/up takes 318k cycles, in which the MFMAs are busy 54% (69% of the 249k cycles in which a CU has
+// waves; QKV and down alike, O 34%); LDS instructions take a fifth of a CU's cycles, without bank
+// conflicts, and a CU pulls 35-45 GB/s of operands, where the former kernel's smaller tiles were held
+// at 65-70. The clock is about 2.1 GHz then; with constant operands the same 302k cycles run at 2.5
+// GHz (118 us for 145). Larger tiles move fewer bytes per MFMA, through LDS as from memory. Hence one
 // workgroup per CU with a large tile (128 x 384 for gate/up: 160 KiB of LDS, 232 workgroups at 512
 // rows), not several small ones. Each wave holds two sets of operand registers: while the MFMAs of a
 // k-step run, the next k-step's operands are read from LDS between them, and the barrier of a k-step
