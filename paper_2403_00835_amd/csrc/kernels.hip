@@ -1179,7 +1179,8 @@ hipError_t launch_attn_prompt(int rows, int max_rows, int tiles, int nseq, int n
     // 190 -> 61 (89); 192 rows behind 1024: 34 -> 28 (36), 8192: 197 -> 137 (254); 256 rows (half the
     // CUs) behind 1024: 36 -> 39 (46), 8192: 196 -> 189 (339). Pieces of two pairs: 64 rows behind 8192
     // keys 88, 512 rows 227 (four pairs 214, no pieces 209, the pair 655). One row behind 2048 keys: 51
-    // -> 22 (17): the pair stays ahead there by its shorter launches, not worth another order of sums.
+    // -> 22 (17): the pair stays ahead there by its shorter launches, not worth another order of sums;
+    // behind 32768: 769 -> 187 (193), 64 rows 730 -> 233 (353).
     const int npiece = (nch + 2 * kPromptPiece - 1) / (2 * kPromptPiece);
     const bool split = nch > 3 * kPromptPiece && 2 * p.n_heads * tiles < kCUs;
     const dim3 grid(p.n_heads, (max_rows + kPromptAttnRows - 1) / kPromptAttnRows, split ? nseq * npiece : nseq);

@@ -3,6 +3,9 @@ product in one launch or over K ranges; a depth of four or two k-steps), 240 and
 256 and 258 gate/up tile pairs (column tiles of one or several 16-column tiles), K shorter than the
 eight waves' first k-steps, in bf16 and fp32. Blocks of 1 to 64 rows take every row-group variant.
 
+Over three row tiles the one-launch down product has 144 or 264 workgroups of 16 columns (264: it takes
+32-column ones).
+
 The logits of each step are compared with the oracle's forward over prompt and block, and a
 batched step (more than 64 rows: the multi-tile products) gives the bits of the single steps.
 Tolerance: the suite's (1e-4 fp32, 2e-2 bf16) on every logit, and in the 2-norm about four times the
@@ -24,10 +27,12 @@ SHAPES = {
     "bf16-k64": ModelConfig(n_layers=2, d_model=768, n_heads=12, head_dim=64, ffn_dim=2048, vocab=512),
     "bf16-k65": ModelConfig(n_layers=1, d_model=1280, n_heads=20, head_dim=64, ffn_dim=2080, vocab=500),
     "bf16-wide": ModelConfig(n_layers=1, d_model=1408, n_heads=22, head_dim=64, ffn_dim=4112, vocab=512),
+    "bf16-two": ModelConfig(n_layers=1, d_model=1408, n_heads=22, head_dim=64, ffn_dim=1500, vocab=512),
     "bf16-k2": ModelConfig(n_layers=2, d_model=64, n_heads=2, head_dim=32, ffn_dim=70, vocab=100),
     # fp32: 16 values a k-step
     "f32-k64": ModelConfig(n_layers=1, d_model=128, n_heads=4, head_dim=32, ffn_dim=1024, vocab=300, dtype="f32"),
     "f32-k65": ModelConfig(n_layers=1, d_model=128, n_heads=4, head_dim=32, ffn_dim=1030, vocab=300, dtype="f32"),
+    "f32-two": ModelConfig(n_layers=1, d_model=1408, n_heads=22, head_dim=64, ffn_dim=600, vocab=300, dtype="f32"),
 }
 BLOCKS = [1, 16, 17, 33, 64]
 REL = {"f32": 1e-6, "bf16": 2.5e-4}
